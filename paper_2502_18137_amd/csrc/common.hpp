@@ -113,12 +113,40 @@ __host__ __device__ inline int range_item(int r0, int len, int p, int Tm, bool c
     return -1;  // p >= len
 }
 
+// Item counters of the attention kernel's work distribution: one per XCD range, 128 bytes apart, set to `start`
+// (the items of each range that the launch's workgroups take without asking) before the launch.  counters null:
+// every item has a workgroup of its own.
+constexpr int QUEUE_PITCH = 32;
+constexpr size_t ATTN_QUEUE_BYTES = 1024;
+static_assert(8 * QUEUE_PITCH * sizeof(unsigned int) == ATTN_QUEUE_BYTES, "eight counters, 128 bytes apart");
+struct AttnQueue {
+    unsigned int* counters;
+    unsigned int start;
+};
+__device__ __forceinline__ void set_queue(const AttnQueue& q) {
+    if (q.counters && threadIdx.x < 8) q.counters[threadIdx.x * QUEUE_PITCH] = q.start;
+}
+
 // ---- kernel launchers (host functions defined next to their kernels) ----------------------------
-// Block statistics of Q (+ optional INT8 quantization of Q): pooled means, self-similarity.
-hipError_t launch_block_stats_q(const void* Q, const Shape& s, double* pooled_q, double* sim_q,
-                                int8_t* Qq, float* q_scale, hipStream_t st);
-// Block statistics of K: per-block channel sums (transposed [B,H,d,Tn]) and self-similarity.
-hipError_t launch_block_stats_k(const void* K, const Shape& s, double* ksum_t, double* sim_k, hipStream_t st);
+// Block statistics of Q and K: pooled means of Q (+ its INT8 quantization if Qq), per-block channel sums of K (transposed
+// [B,H,d,Tn]), self-similarities; the item counters of the attention launch to come if queue has any.  sim_q null: only
+// what the quantization of Q and the mean of K need (Qq, q_scale, ksum_t).
+hipError_t launch_block_stats(const void* Q, const void* K, const Shape& s, double* pooled_q, double* ksum_t,
+                              double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, AttnQueue queue, hipStream_t st);
+// Short calls take the block statistics (and V tiles) in one launch and the predictor with the K quantization in
+// another.  Up to 256 key blocks (a row's logits fit the LDS of a workgroup of 8 rows at full occupancy) and as many
+// elements per tensor as below: a launch, an event and a wait saved are then worth more than what the passes lose in one
+// kernel (the registers of the hungriest, the mean summed once per workgroup).  Whole forward passes, several launches
+// on two streams against these: 67 / 32 us at 2 x 2048 x 64, 191 / 170 at 24 x 4173 x 128, 378 / 348 at 8 x 16384 x 64,
+// 199 / 183 at 48 x 3000 x 128, 172 / 166 at 192 x 1024 x 128; beyond the line 750 / 776 at 12 x 16000 x 128,
+// 595 / 603 at 32 x 8192 x 128, 218 / 218 at 256 x 1024 x 128.
+inline bool short_call(const Shape& s) {
+    return s.Tn <= 256 && (long long)s.B * s.H * s.N * s.d <= (s.Tn <= 128 ? 3ll << 23 : 1ll << 24);
+}
+// Short calls: all of launch_block_stats in one launch, with V re-tiled as launch_v_tiles does if v_tiles.
+hipError_t launch_prep(const void* Q, const void* K, const void* V, const Shape& s, double* pooled_q, double* ksum_t,
+                       double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, uint16_t* v_tiles, AttnQueue queue,
+                       hipStream_t st);
 // Token mean of K per (b,h) from the block sums.
 hipError_t launch_k_mean(const double* ksum_t, const Shape& s, float* k_mean, hipStream_t st);
 // INT8 quantization of K - k_mean.
@@ -131,20 +159,25 @@ hipError_t launch_logits(const double* pooled_q, const double* ksum_t, const Sha
 hipError_t launch_topcdf(const double* logits, const double* sim_q, const double* sim_k, const Shape& s,
                          const HeadParams& tau, const HeadParams& theta, int causal, uint8_t* mask,
                          hipStream_t st);
+// Short calls: logits, TopCdf and the K quantization (mean included; none if Kq is null) in one launch.
+hipError_t launch_predict_quant(const double* pooled_q, const double* ksum_t, const double* sim_q, const double* sim_k,
+                                const void* K, const Shape& s, const HeadParams& tau, const HeadParams& theta,
+                                float sm_scale, int causal, uint8_t* mask, int8_t* Kq, float* k_scale, hipStream_t st);
 // V [B,H,N,d] (strided) -> per key block, d rows of 64 key slots in the order the P~V MFMA consumes.
 hipError_t launch_v_tiles(const void* V, const Shape& s, uint16_t* v_tiles, hipStream_t st);
 // lut[b,h,i,:] = the j with mask[b,h,i,j] != 0, ascending, then -1; lut_count[b,h,i] = how many.
 hipError_t launch_mask_lut(const uint8_t* mask, const Shape& s, int32_t* lut, int32_t* lut_count, hipStream_t st);
 // stats[0..n) = 0 (a fill kernel, not a memset node, so callers may capture it in a graph).
 hipError_t launch_zero_stats(unsigned long long* stats, int n, hipStream_t st);
-// The sparse flash loop (accumulates into stats).  queue: ATTN_QUEUE_BYTES of device memory for the item
-// counters of the work distribution, cleared here by a fill kernel in front of the launch; it must not be
-// shared with another launch that may run at the same time.
-constexpr size_t ATTN_QUEUE_BYTES = 1024;
+// The item counters an attention launch of this shape needs, in ATTN_QUEUE_BYTES of device memory at `memory` that no
+// other launch may use at the same time; they have to be set (launch_prep, launch_set_queue) before the launch.
+hipError_t plan_queue(const Shape& s, unsigned int* memory, AttnQueue* queue);
+hipError_t launch_set_queue(const AttnQueue& queue, hipStream_t st);
+// The sparse flash loop (accumulates into stats).
 hipError_t launch_attn(const void* Qp, const void* Kp, const float* q_scale, const float* k_scale,
                        const void* v_tiles, const float* v_scale, const Shape& s, const uint8_t* mask,
                        const HeadParams& lambda, float sm_scale, int causal, void* O, unsigned long long* stats,
-                       unsigned int* queue, hipStream_t st);
+                       const AttnQueue& queue, hipStream_t st);
 // FP8 form of V: per-(b,h,channel) |V| maxima (as fp32 bit patterns, zeroed here), scales amax/448, and
 // E4M3 tiles in the operand order of the 32x32x64 MFMA.
 hipError_t launch_v_tiles_fp8(const void* V, const Shape& s, unsigned char* tiles, float* v_scale,

@@ -4,7 +4,7 @@
 //            prefix sum, fix-block overrides, causal rules.
 // All arithmetic is fp64 so that block decisions agree with an fp64 reference except for
 // statistics that sit within ~1e-13 of a threshold.
-#include "common.hpp"
+#include "lanes.hpp"
 
 namespace sparge {
 
@@ -358,11 +358,124 @@ __device__ __forceinline__ void bitonic_sort(unsigned long long (&key)[EPL], int
     if constexpr (K < 64 * EPL) bitonic_sort<EPL, 2 * K>(key, lane);
 }
 
-// TopCdf with one mask row per wave and the sort in registers: lane L holds the EPL consecutive ranks
+// maximum over the wave (every lane gets it)
+template <int PARTNER>
+__device__ __forceinline__ double max_of_partner(double v) {
+    const uint32_t lo = static_cast<uint32_t>(__double2loint(v)), hi = static_cast<uint32_t>(__double2hiint(v));
+    if constexpr (PARTNER >= 16) {
+        uint32_t l0, l1, h0, h1;
+        swap_pair<PARTNER>(lo, l0, l1);
+        swap_pair<PARTNER>(hi, h0, h1);
+        return fmax(__hiloint2double(static_cast<int>(h0), static_cast<int>(l0)),
+                    __hiloint2double(static_cast<int>(h1), static_cast<int>(l1)));
+    } else {
+        return fmax(v, __hiloint2double(static_cast<int>(row_xchg<PARTNER>(hi)), static_cast<int>(row_xchg<PARTNER>(lo))));
+    }
+}
+__device__ __forceinline__ double wave_max(double v) {
+    v = max_of_partner<1>(v);
+    v = max_of_partner<2>(v);
+    v = max_of_partner<7>(v);
+    v = max_of_partner<15>(v);
+    v = max_of_partner<16>(v);
+    return max_of_partner<32>(v);
+}
+
+// TopCdf of one mask row by one wave, the sort in registers: lane L holds the EPL consecutive ranks
 // L * EPL .. L * EPL + EPL - 1 as 64-bit keys (see topcdf_kernel for the key).  A bitonic stage at a distance
 // below EPL exchanges inside a lane (compile-time register indices), a larger one takes the partner
 // lane's key with DPP moves or lane swaps (vector ALU: with ds_bpermute the LDS pipeline was the limit);
 // nothing but the final flags and the exact probabilities goes through LDS, and no workgroup barrier is needed.  Same comparisons, hence the same order, as the LDS version.
+// row_at(j): the row's logit of key block j; pval, flag: 64 * EPL entries of LDS of this wave's own (pval may be
+// where row_at reads from: all logits are read before the first probability is written).
+template <int EPL, class RowAt>
+__device__ __forceinline__ void topcdf_row(RowAt row_at, const int i, const double sim_q_i, const double* __restrict__ sk,
+                                           const Shape& s, const double tau, const double theta, const int causal,
+                                           const int lane, double* pval, uint8_t* flag, uint8_t* __restrict__ out) {
+    const double NEG = -__builtin_inf();
+    if (sim_q_i < theta) {   // a query block that is not self-similar keeps every visible key block
+        for (int j = lane; j < s.Tn; j += 64) out[j] = (causal && j * BK > i * BQ + (BQ - 1)) ? 0 : 1;
+        return;
+    }
+    // 1.-2. masked logits, softmax, probabilities (entries lane * EPL + e: a lane reads one contiguous piece)
+    double x[EPL];
+    double mx = NEG;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        const int j = lane * EPL + e;
+        x[e] = NEG;
+        if (j < s.Tn) {
+            x[e] = row_at(j);
+            if (sk[j] < theta) x[e] = NEG;
+            if (causal && j * BK > i * BQ + (BQ - 1)) x[e] = NEG;
+        }
+        mx = fmax(mx, x[e]);
+    }
+    mx = wave_max(mx);
+    double z = 0.0;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        x[e] = (x[e] == NEG) ? 0.0 : exp(x[e] - mx);
+        z += x[e];
+    }
+    z = group_sum<64>(z);
+    // (one division per lane; x * (1 / z) is within two roundings of x / z, far inside the band in which a
+    // TopCdf decision counts as undecided)
+    const double rz = z > 0.0 ? 1.0 / z : 0.0;
+    double tot = 0.0;
+    unsigned long long key[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        const int j = lane * EPL + e;
+        const double p = j < s.Tn ? x[e] * rz : 0.0;
+        tot += p;
+        pval[j] = p;
+        flag[j] = 0;
+        key[e] = j < s.Tn ? ((static_cast<unsigned long long>(__double_as_longlong(p)) & ~0xFFFFull) |
+                             static_cast<unsigned long long>(0xFFFF - j))
+                          : 0ull;   // padding ranks last
+    }
+    tot = group_sum<64>(tot);
+
+    // 3. bitonic sort, descending by key
+    bitonic_sort<EPL>(key, lane);
+
+    // 4. exclusive prefix mass per rank (exact probabilities by index); rank kept iff mass before it < tau * total
+    double pv[EPL];
+    double local = 0.0;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        pv[e] = key[e] ? pval[0xFFFF - static_cast<int>(key[e] & 0xFFFFull)] : 0.0;
+        local += pv[e];
+    }
+    double incl = local;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const double o = shfl_up_f64(incl, d);
+        if (lane >= d) incl += o;
+    }
+    double before = incl - local;
+    const double thresh = tau * tot;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        if (pv[e] > 0.0 && before < thresh) flag[0xFFFF - static_cast<int>(key[e] & 0xFFFFull)] = 1;
+        before += pv[e];
+    }
+    __builtin_amdgcn_wave_barrier();   // the flags are read back by other lanes of this wave only
+
+    // 5. fix-block overrides and causal rules, then the row goes out
+    for (int j = lane; j < s.Tn; j += 64) {
+        uint8_t m = flag[j];
+        if (sk[j] < theta) m = 1;
+        if (causal) {
+            if (j * BK > i * BQ + (BQ - 1)) m = 0;
+            if (j == (i * BQ) / BK) m = 1;
+        }
+        out[j] = m;
+    }
+}
+
+// One mask row per wave, the logits from memory.
 template <int EPL>
 __global__ __launch_bounds__(256) void topcdf_wave_kernel(const double* __restrict__ logits,
                                                            const double* __restrict__ sim_q,
@@ -378,98 +491,100 @@ __global__ __launch_bounds__(256) void topcdf_wave_kernel(const double* __restri
     const int i = rowid % s.Tm;
     const long long bh = rowid / s.Tm;
     const int h = static_cast<int>(bh % s.H);
-    const double tau = static_cast<double>(tau_h.v[h]);
-    const double theta = static_cast<double>(theta_h.v[h]);
     const double* row = logits + (long long)rowid * s.Tn;
-    const double* sk = sim_k + bh * s.Tn;
-    uint8_t* out = mask + (long long)rowid * s.Tn;
-    const double NEG = -__builtin_inf();
-    if (sim_q[rowid] < theta) {   // a query block that is not self-similar keeps every visible key block
-        for (int j = lane; j < s.Tn; j += 64) out[j] = (causal && j * BK > i * BQ + (BQ - 1)) ? 0 : 1;
+    topcdf_row<EPL>([&](int j) { return row[j]; }, i, sim_q[rowid], sim_k + bh * s.Tn, s, static_cast<double>(tau_h.v[h]),
+                    static_cast<double>(theta_h.v[h]), causal, lane, pval[wave], flag[wave],
+                    mask + (long long)rowid * s.Tn);
+}
+
+// The predictor of short rows in one launch, and beside it the K quantization, which waits for the same block
+// statistics: the first n_pred workgroups take R mask rows each (the logits of the 16 x 16 tiles over these rows
+// by R waves into LDS, then one row per wave), the others quantize `per_wg` K blocks of one head, with the head's
+// token mean of K computed on the spot (in the order k_mean_kernel adds: the same bits).
+// What bounds it is latency: the logits' operand loads, one chain of d / 4 fp64 matrix products, the softmax's
+// reductions and the sort's stages, one after the other; logits through memory and a launch for each of the
+// four passes came on top of that.
+template <int D, int DT, int EPL, int R>
+__global__ __launch_bounds__(64 * R) void predict_quant_kernel(
+    const double* __restrict__ pooled_q, const double* __restrict__ ksum_t, const double* __restrict__ sim_q,
+    const double* __restrict__ sim_k, const uint16_t* __restrict__ K, Shape s, double sm_scale, HeadParams tau_h,
+    HeadParams theta_h, int causal, int n_pred, int per_wg, uint8_t* __restrict__ mask, int8_t* __restrict__ Kq,
+    float* __restrict__ k_scale) {
+    constexpr int NPAD = 64 * EPL;
+    static_assert(R % 4 == 0 && R <= 16, "rows of one 16-row tile, whole groups of 256 threads");
+    struct Rows {
+        double lg[R][NPAD];       // logits, then probabilities
+        uint8_t flag[R][NPAD];
+    };
+    struct Quant {
+        float mean[D];
+        float amax[2][R / 4][4];
+    };
+    __shared__ __align__(16) union {
+        Rows rows;
+        Quant quant;
+    } lds;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    int id = blockIdx.x;
+    if (id < n_pred) {
+        const int groups = (s.Tm + R - 1) / R;
+        const long long bh = id / groups;
+        const int i0 = id % groups * R, l16 = lane & 15, kk = lane >> 4;
+        const double* qrow = pooled_q + (bh * s.Tm + min(i0 + l16, s.Tm - 1)) * D + kk;   // rows past Tm or R: not used
+#pragma unroll 1
+        for (int j0 = wave * 16; j0 < s.Tn; j0 += 16 * R) {
+            const double* kcol = ksum_t + bh * D * s.Tn + (long long)kk * s.Tn + min(j0 + l16, s.Tn - 1);
+            v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int c = 0; c < D; c += 4)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qrow[c], kcol[(long long)c * s.Tn], acc, 0, 0, 0);
+            const int j = j0 + l16;
+            if (j < s.Tn) {
+                const double cnt = static_cast<double>(min(BK, s.N - j * BK));
+#pragma unroll
+                for (int r = 0; r < R / 4; ++r) lds.rows.lg[4 * r + kk][j] = sm_scale * (acc[r] / cnt);
+            }
+        }
+        __syncthreads();
+        const int i = i0 + wave, h = static_cast<int>(bh % s.H);
+        if (i >= s.Tm) return;
+        const double* row = lds.rows.lg[wave];
+        topcdf_row<EPL>([&](int j) { return row[j]; }, i, sim_q[bh * s.Tm + i], sim_k + bh * s.Tn, s,
+                        static_cast<double>(tau_h.v[h]), static_cast<double>(theta_h.v[h]), causal, lane,
+                        lds.rows.lg[wave], lds.rows.flag[wave], mask + (bh * s.Tm + i) * s.Tn);
         return;
     }
-    auto wave_sum = [&](double v) {
+    id -= n_pred;
+    const int wgs = (s.Tn + per_wg - 1) / per_wg;
+    const long long bh = id / wgs;
+    const int t0 = id % wgs * per_wg;
+    // token mean of K: 16 lanes per channel; lane l of them holds the partial sums that lanes l, l + 16, l + 32
+    // and l + 48 of k_mean_kernel hold, combined as there
+    for (int c = threadIdx.x >> 4; c < D; c += 4 * R) {
+        const double* row = ksum_t + (bh * D + c) * s.Tn;
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int m = 1; m < 64; m <<= 1) v += shfl_xor_f64(v, m);
-        return v;
-    };
-    // 1.-2. masked logits, softmax, probabilities (entries lane * EPL + e: a lane reads one contiguous piece)
-    double x[EPL];
-    double mx = NEG;
+        for (int e = 0; e < EPL; ++e)
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        const int j = lane * EPL + e;
-        x[e] = NEG;
-        if (j < s.Tn) {
-            x[e] = row[j];
-            if (sk[j] < theta) x[e] = NEG;
-            if (causal && j * BK > i * BQ + (BQ - 1)) x[e] = NEG;
-        }
-        mx = fmax(mx, x[e]);
+            for (int q = 0; q < 4; ++q) {
+                const int j = 64 * e + 16 * q + (lane & 15);
+                if (j < s.Tn) a[q] += row[j];
+            }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[q] = group_sum<16>(a[q]);
+        const double sum = (a[0] + a[1]) + (a[2] + a[3]);
+        if ((lane & 15) == 0) lds.quant.mean[c] = static_cast<float>(sum / static_cast<double>(s.N));
     }
+    __syncthreads();
+    const int tid = threadIdx.x & 255, part = threadIdx.x >> 8, cchunk = tid % (D / 8);
+    float mean[8];
 #pragma unroll
-    for (int m = 1; m < 64; m <<= 1) mx = fmax(mx, shfl_xor_f64(mx, m));
-    double z = 0.0;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        x[e] = (x[e] == NEG) ? 0.0 : exp(x[e] - mx);
-        z += x[e];
-    }
-    z = wave_sum(z);
-    // (one division per lane; x * (1 / z) is within two roundings of x / z, far inside the band in which a
-    // TopCdf decision counts as undecided)
-    const double rz = z > 0.0 ? 1.0 / z : 0.0;
-    double tot = 0.0;
-    unsigned long long key[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        const int j = lane * EPL + e;
-        const double p = j < s.Tn ? x[e] * rz : 0.0;
-        tot += p;
-        pval[wave][j] = p;
-        flag[wave][j] = 0;
-        key[e] = j < s.Tn ? ((static_cast<unsigned long long>(__double_as_longlong(p)) & ~0xFFFFull) |
-                             static_cast<unsigned long long>(0xFFFF - j))
-                          : 0ull;   // padding ranks last
-    }
-    tot = wave_sum(tot);
-
-    // 3. bitonic sort, descending by key
-    bitonic_sort<EPL>(key, lane);
-
-    // 4. exclusive prefix mass per rank (exact probabilities by index); rank kept iff mass before it < tau * total
-    double pv[EPL];
-    double local = 0.0;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        pv[e] = key[e] ? pval[wave][0xFFFF - static_cast<int>(key[e] & 0xFFFFull)] : 0.0;
-        local += pv[e];
-    }
-    double incl = local;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const double o = shfl_up_f64(incl, d);
-        if (lane >= d) incl += o;
-    }
-    double before = incl - local;
-    const double thresh = tau * tot;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        if (pv[e] > 0.0 && before < thresh) flag[wave][0xFFFF - static_cast<int>(key[e] & 0xFFFFull)] = 1;
-        before += pv[e];
-    }
-    __builtin_amdgcn_wave_barrier();   // the flags are read back by other lanes of this wave only
-
-    // 5. fix-block overrides and causal rules, then the row goes out
-    for (int j = lane; j < s.Tn; j += 64) {
-        uint8_t m = flag[wave][j];
-        if (sk[j] < theta) m = 1;
-        if (causal) {
-            if (j * BK > i * BQ + (BQ - 1)) m = 0;
-            if (j == (i * BQ) / BK) m = 1;
-        }
-        out[j] = m;
-    }
+    for (int e = 0; e < 8; ++e) mean[e] = lds.quant.mean[cchunk * 8 + e];
+    const uint16_t* base = K + (bh / s.H) * s.sb + (bh % s.H) * s.sh;
+    const int t1 = min(t0 + per_wg, s.Tn);
+    int turn = 0;   // two sets of block maxima in turn: one barrier per block
+    for (int t = t0; t < t1; t += R / 4, turn ^= 1)
+        quant_k_block<D, DT>(base, s, bh, t + part < t1 ? t + part : s.Tn, tid, mean, lds.quant.amax[turn][part], Kq, k_scale);
 }
 
 // The mask as an index list: one wave per mask row compacts the kept block indices with ballots, 64 entries
@@ -537,6 +652,34 @@ hipError_t launch_topcdf(const double* logits, const double* sim_q, const double
     dim3 grid(s.Tm, s.H, s.B);
     hipLaunchKernelGGL(topcdf_kernel, grid, dim3(256), smem, st, logits, sim_q, sim_k, s, tau, theta, causal,
                        npad, mask);
+    return hipGetLastError();
+}
+
+hipError_t launch_predict_quant(const double* pooled_q, const double* ksum_t, const double* sim_q, const double* sim_k,
+                                const void* K, const Shape& s, const HeadParams& tau, const HeadParams& theta,
+                                float sm_scale, int causal, uint8_t* mask, int8_t* Kq, float* k_scale, hipStream_t st) {
+    if (!short_call(s)) return hipErrorInvalidValue;
+    constexpr int R = 8;   // 4 and 16 rows per workgroup: within 3 % of it, either side (33.4 / 31.6 / 31.3 us a call at
+                         // 2 x 2048 x 64 with 16 / 8 / 4, 168 / 168 / 170 us at 24 x 4173 x 128)
+    const int BH = s.B * s.H, n_pred = BH * ((s.Tm + R - 1) / R);
+    // K blocks per workgroup: enough that reading the block sums for the mean (8 d T_n bytes) stays below reading
+    // the blocks themselves (128 d bytes each)
+    int per_wg = (s.Tn + 15) / 16;
+    per_wg = (per_wg + R / 4 - 1) / (R / 4) * (R / 4);
+    const int n_quant = Kq ? BH * ((s.Tn + per_wg - 1) / per_wg) : 0;
+    const double scale = sm_scale > 0.f ? static_cast<double>(sm_scale) : 1.0 / sqrt(static_cast<double>(s.d));
+    const uint16_t* X = static_cast<const uint16_t*>(K);
+#define CALLE(D, DT, EPL)                                                                                          \
+    hipLaunchKernelGGL((predict_quant_kernel<D, DT, EPL, R>), dim3(n_pred + n_quant), dim3(64 * R), 0, st, pooled_q, \
+                       ksum_t, sim_q, sim_k, X, s, scale, tau, theta, causal, n_pred, per_wg, mask, Kq, k_scale)
+#define CALL(D, DT) { if (s.Tn <= 128) CALLE(D, DT, 2); else CALLE(D, DT, 4); }
+    if (s.d == 64 && s.dtype == SPARGE_F16) CALL(64, SPARGE_F16)
+    else if (s.d == 64 && s.dtype == SPARGE_BF16) CALL(64, SPARGE_BF16)
+    else if (s.d == 128 && s.dtype == SPARGE_F16) CALL(128, SPARGE_F16)
+    else if (s.d == 128 && s.dtype == SPARGE_BF16) CALL(128, SPARGE_BF16)
+    else return hipErrorInvalidValue;
+#undef CALL
+#undef CALLE
     return hipGetLastError();
 }
 
