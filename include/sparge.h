@@ -145,8 +145,8 @@ int sparge_predict_static(const void* Q, const void* K, const sparge_desc* desc,
  * P~V row-group products executed, tiles a full attention needs, row-group products a full
  * attention needs}; it is overwritten, not accumulated.
  * Work distribution: the launch is two resident workgroups per compute unit that take (head, Q block)
- * items from eight counters (one per XCD range of items) kept in `ws` and cleared by a one-wave kernel
- * enqueued in front of the launch; which workgroup computes an item depends on timing, the result does not.
+ * items from eight counters (one per XCD range of items) kept in `ws` and set by an earlier kernel of the call
+ * in front of the launch; which workgroup computes an item depends on timing, the result does not.
  */
 int sparge_attn_quantized(const int8_t* Qq, const int8_t* Kq, const float* q_scale, const float* k_scale,
                           const void* V, const sparge_desc* desc, const uint8_t* mask,

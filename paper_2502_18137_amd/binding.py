@@ -229,7 +229,7 @@ def sparge_attn_quantized(Qq, Kq, q_scale, k_scale, V: torch.Tensor, mask: Optio
         raise SpargeError("mask must be a contiguous uint8 [B,H,Tm,Tn] tensor")
     O = torch.empty_like(V) if out is None else out
     _same_layout(V, O)
-    stats = torch.zeros((B, H, 4), dtype=torch.int64, device=V.device) if return_stats else None
+    stats = torch.empty((B, H, 4), dtype=torch.int64, device=V.device) if return_stats else None
     ws = _workspace(V, WS_ATTN_QUANTIZED, ws, pv_fp8)
     _check(load_library().sparge_attn_quantized(_ptr(Qq), _ptr(Kq), _ptr(q_scale), _ptr(k_scale), _ptr(V),
                                                 ctypes.byref(d), _ptr(mask), _per_head(lam, H), float(sm_scale),
@@ -304,7 +304,7 @@ def sparge_attn(Q, K, V, mask: Optional[torch.Tensor], lam, causal: bool = False
         raise SpargeError("mask must be a contiguous uint8 [B,H,Tm,Tn] tensor")
     O = torch.empty_like(V) if out is None else out
     _same_layout(V, O)
-    stats = torch.zeros((B, H, 4), dtype=torch.int64, device=Q.device) if return_stats else None
+    stats = torch.empty((B, H, 4), dtype=torch.int64, device=Q.device) if return_stats else None
     ws = _workspace(Q, WS_ATTN, ws, pv_fp8)
     _check(load_library().sparge_attn(_ptr(Q), _ptr(K), _ptr(V), ctypes.byref(d), _ptr(mask), _per_head(lam, H),
                                       float(sm_scale), int(causal), _ptr(O), _ptr(stats), _ptr(ws), ws.numel(),
@@ -323,7 +323,7 @@ def sparge_forward(Q, K, V, tau, theta, lam, causal: bool = False, sm_scale: flo
     O = torch.empty_like(V) if out is None else out
     _same_layout(V, O)
     mask = torch.empty((B, H, Tm, Tn), dtype=torch.uint8, device=Q.device) if return_mask else None
-    stats = torch.zeros((B, H, 4), dtype=torch.int64, device=Q.device) if return_stats else None
+    stats = torch.empty((B, H, 4), dtype=torch.int64, device=Q.device) if return_stats else None
     ws = _workspace(Q, WS_FORWARD, ws, pv_fp8)
     _check(load_library().sparge_forward(_ptr(Q), _ptr(K), _ptr(V), ctypes.byref(d), _per_head(tau, H),
                                          _per_head(theta, H), _per_head(lam, H), float(sm_scale), int(causal),

@@ -223,11 +223,11 @@ int static_scratch(void** out) {
 
 int run_stats_and_quant(const void* Q, const void* K, const Shape& s, double* pooled_q, double* ksum_t,
                         double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, int8_t* Kq, float* k_scale,
-                        float* k_mean, const AttnQueue& queue, hipStream_t st) {
+                        float* k_mean, const AttnStart& start, hipStream_t st) {
     hipError_t e;
     e = sim_q && short_call(s)
-            ? launch_prep(Q, K, nullptr, s, pooled_q, ksum_t, sim_q, sim_k, Qq, q_scale, nullptr, queue, st)
-            : launch_block_stats(Q, K, s, pooled_q, ksum_t, sim_q, sim_k, Qq, q_scale, queue, st);
+            ? launch_prep(Q, K, nullptr, s, pooled_q, ksum_t, sim_q, sim_k, Qq, q_scale, nullptr, start, st)
+            : launch_block_stats(Q, K, s, pooled_q, ksum_t, sim_q, sim_k, Qq, q_scale, start, st);
     if (e != hipSuccess) return hip_fail(e, "block statistics");
     if (Kq) {
         if ((e = launch_k_mean(ksum_t, s, k_mean, st)) != hipSuccess) return hip_fail(e, "k_mean");
@@ -246,26 +246,28 @@ int run_predict(const Shape& s, void* ws, const Workspace& w, const HeadParams& 
     return SPARGE_OK;
 }
 
-// The item counters of an attention launch whose call has no earlier kernel that could set them.
-int set_queue_for(const Shape& s, unsigned int* memory, AttnQueue* queue, hipStream_t st) {
-    hipError_t e;
-    if ((e = plan_queue(s, memory, queue)) != hipSuccess) return hip_fail(e, "plan queue");
-    if ((e = launch_set_queue(*queue, st)) != hipSuccess) return hip_fail(e, "set queue");
-    return SPARGE_OK;
+int plan_attn(const Shape& s, void* queue, uint64_t* stats, AttnStart* start) {
+    const hipError_t e = plan_start(s, static_cast<unsigned int*>(queue), reinterpret_cast<unsigned long long*>(stats), start);
+    return e == hipSuccess ? SPARGE_OK : hip_fail(e, "plan of the attention launch");
+}
+// The same for an attention launch whose call has no earlier kernel that could set its counters.
+int plan_and_set_attn(const Shape& s, void* queue, uint64_t* stats, AttnStart* start, hipStream_t st) {
+    const int rc = plan_attn(s, queue, stats, start);
+    if (rc) return rc;
+    const hipError_t e = launch_set_start(*start, st);
+    return e == hipSuccess ? SPARGE_OK : hip_fail(e, "set the attention launch's counters");
 }
 
-// The attention launch, bracketed by the caller's timing events when some are installed.  queue: already set.
+// The attention launch, bracketed by the caller's timing events when some are installed.  start: set already.
 int timed_attn(const void* Qq, const void* Kq, const float* q_scale, const float* k_scale,
                const void* v_tiles, const Shape& s, const uint8_t* mask, const HeadParams& lam, float sm_scale,
-               int causal, void* O, uint64_t* stats, const AttnQueue& queue, hipStream_t st) {
+               int causal, void* O, uint64_t* stats, const AttnStart& start, hipStream_t st) {
     const bool timed = g_ev_start && g_ev_k < g_ev_n;
     hipError_t e;
-    if (stats && (e = launch_zero_stats(reinterpret_cast<unsigned long long*>(stats), s.B * s.H * 4, st)) != hipSuccess)
-        return hip_fail(e, "zero stats");
     if (timed && (e = hipEventRecord(static_cast<hipEvent_t>(g_ev_start[g_ev_k]), st)) != hipSuccess)
         return hip_fail(e, "record start event");
     if ((e = launch_attn(Qq, Kq, q_scale, k_scale, v_tiles, v_scale_of(v_tiles, s), s, mask, lam, sm_scale, causal, O,
-                         reinterpret_cast<unsigned long long*>(stats), queue, st)) != hipSuccess)
+                         reinterpret_cast<unsigned long long*>(stats), start, st)) != hipSuccess)
         return hip_fail(e, "attn");
     if (timed) {
         if ((e = hipEventRecord(static_cast<hipEvent_t>(g_ev_stop[g_ev_k]), st)) != hipSuccess)
@@ -277,10 +279,10 @@ int timed_attn(const void* Qq, const void* Kq, const float* q_scale, const float
 
 int run_attn(const void* Qq, const void* Kq, const float* q_scale, const float* k_scale, const void* V,
              const Shape& s, void* v_tiles, const uint8_t* mask, const HeadParams& lam, float sm_scale,
-             int causal, void* O, uint64_t* stats, const AttnQueue& queue, hipStream_t st) {
+             int causal, void* O, uint64_t* stats, const AttnStart& start, hipStream_t st) {
     hipError_t e;
     if ((e = retile_v(V, s, v_tiles, st)) != hipSuccess) return hip_fail(e, "v_tiles");
-    return timed_attn(Qq, Kq, q_scale, k_scale, v_tiles, s, mask, lam, sm_scale, causal, O, stats, queue, st);
+    return timed_attn(Qq, Kq, q_scale, k_scale, v_tiles, s, mask, lam, sm_scale, causal, O, stats, start, st);
 }
 
 }  // namespace
@@ -311,7 +313,7 @@ int sparge_quantize(const void* Q, const void* K, const sparge_desc* desc, int8_
         return fail(SPARGE_EINVAL, "tensor pointers must be 16-byte aligned");
     const Workspace w = plan(s, SPARGE_WS_QUANTIZE);
     if ((rc = check_ws(w, ws, ws_bytes))) return rc;
-    return run_stats_and_quant(Q, K, s, nullptr, at<double>(ws, w.ksum_t), nullptr, nullptr, Qq, q_scale, Kq, k_scale, k_mean, AttnQueue{},
+    return run_stats_and_quant(Q, K, s, nullptr, at<double>(ws, w.ksum_t), nullptr, nullptr, Qq, q_scale, Kq, k_scale, k_mean, AttnStart{},
                                static_cast<hipStream_t>(hip_stream));
 }
 
@@ -330,7 +332,7 @@ int sparge_predict(const void* Q, const void* K, const sparge_desc* desc, const 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if ((rc = run_stats_and_quant(Q, K, s, at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t),
                                   at<double>(ws, w.sim_q), at<double>(ws, w.sim_k), nullptr, nullptr, nullptr,
-                                  nullptr, nullptr, AttnQueue{}, st))) return rc;
+                                  nullptr, nullptr, AttnStart{}, st))) return rc;
     const size_t BH = (size_t)s.B * s.H;
     hipError_t e;
     if (short_call(s)) {
@@ -407,10 +409,10 @@ int sparge_attn_quantized(const int8_t* Qq, const int8_t* Kq, const float* q_sca
     const Workspace w = plan(s, SPARGE_WS_ATTN_QUANTIZED);
     if ((rc = check_ws(w, ws, ws_bytes))) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    AttnQueue queue;
-    if ((rc = set_queue_for(s, at<unsigned int>(ws, w.queue), &queue, st))) return rc;
+    AttnStart start;
+    if ((rc = plan_and_set_attn(s, at<void>(ws, w.queue), stats, &start, st))) return rc;
     return run_attn(Qq, Kq, q_scale, k_scale, V, s, at<char>(ws, w.v_tiles), mask, lam, sm_scale, causal, O,
-                    stats, queue, st);
+                    stats, start, st);
 }
 
 int sparge_v_tiles_bytes(const sparge_desc* desc, size_t* bytes) {
@@ -447,9 +449,9 @@ int sparge_attn_tiled(const int8_t* Qq, const int8_t* Kq, const float* q_scale, 
     const Workspace w = plan(s, SPARGE_WS_ATTN_TILED);
     if ((rc = check_ws(w, ws, ws_bytes))) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    AttnQueue queue;
-    if ((rc = set_queue_for(s, at<unsigned int>(ws, w.queue), &queue, st))) return rc;
-    return timed_attn(Qq, Kq, q_scale, k_scale, v_tiles, s, mask, lam, sm_scale, causal, O, stats, queue, st);
+    AttnStart start;
+    if ((rc = plan_and_set_attn(s, at<void>(ws, w.queue), stats, &start, st))) return rc;
+    return timed_attn(Qq, Kq, q_scale, k_scale, v_tiles, s, mask, lam, sm_scale, causal, O, stats, start, st);
 }
 
 int sparge_attn(const void* Q, const void* K, const void* V, const sparge_desc* desc, const uint8_t* mask,
@@ -466,19 +468,18 @@ int sparge_attn(const void* Q, const void* K, const void* V, const sparge_desc* 
     const Workspace w = plan(s, SPARGE_WS_ATTN);
     if ((rc = check_ws(w, ws, ws_bytes))) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    AttnQueue queue;
+    AttnStart start;
     if (s.qk16) {  // the products run on Q and K as they are: nothing to quantize
-        if ((rc = set_queue_for(s, at<unsigned int>(ws, w.queue), &queue, st))) return rc;
+        if ((rc = plan_and_set_attn(s, at<void>(ws, w.queue), stats, &start, st))) return rc;
         return run_attn(Q, K, nullptr, nullptr, V, s, at<char>(ws, w.v_tiles), mask, lam, sm_scale, causal, O, stats,
-                        queue, st);
+                        start, st);
     }
-    hipError_t e;
-    if ((e = plan_queue(s, at<unsigned int>(ws, w.queue), &queue)) != hipSuccess) return hip_fail(e, "plan queue");
+    if ((rc = plan_attn(s, at<void>(ws, w.queue), stats, &start))) return rc;
     if ((rc = run_stats_and_quant(Q, K, s, nullptr, at<double>(ws, w.ksum_t), nullptr, nullptr, at<int8_t>(ws, w.Qq),
                                   at<float>(ws, w.q_scale), at<int8_t>(ws, w.Kq), at<float>(ws, w.k_scale),
-                                  at<float>(ws, w.k_mean), queue, st))) return rc;
+                                  at<float>(ws, w.k_mean), start, st))) return rc;
     return run_attn(at<int8_t>(ws, w.Qq), at<int8_t>(ws, w.Kq), at<float>(ws, w.q_scale), at<float>(ws, w.k_scale),
-                    V, s, at<char>(ws, w.v_tiles), mask, lam, sm_scale, causal, O, stats, queue, st);
+                    V, s, at<char>(ws, w.v_tiles), mask, lam, sm_scale, causal, O, stats, start, st);
 }
 
 int sparge_forward(const void* Q, const void* K, const void* V, const sparge_desc* desc, const float* tau,
@@ -504,22 +505,22 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
     const float* ksc = q8 ? at<float>(ws, w.k_scale) : nullptr;
     int8_t* Qq = q8 ? at<int8_t>(ws, w.Qq) : nullptr;
     float* q_scale = q8 ? at<float>(ws, w.q_scale) : nullptr;
-    AttnQueue queue;
+    AttnStart start;
     hipError_t e;
-    if ((e = plan_queue(s, at<unsigned int>(ws, w.queue), &queue)) != hipSuccess) return hip_fail(e, "plan queue");
+    if ((rc = plan_attn(s, at<void>(ws, w.queue), stats, &start))) return rc;
     if (short_call(s)) {
         // Three launches on the caller's stream: block statistics with the V tiles; predictor beside the K
         // quantization; attention.  (The FP8 tiles need V's maxima first: launches of their own.)
         if (s.pv_fp8 && (e = retile_v(V, s, at<char>(ws, w.v_tiles), st)) != hipSuccess) return hip_fail(e, "v_tiles");
         if ((e = launch_prep(Q, K, V, s, at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t), at<double>(ws, w.sim_q),
-                             at<double>(ws, w.sim_k), Qq, q_scale, s.pv_fp8 ? nullptr : at<uint16_t>(ws, w.v_tiles), queue,
+                             at<double>(ws, w.sim_k), Qq, q_scale, s.pv_fp8 ? nullptr : at<uint16_t>(ws, w.v_tiles), start,
                              st)) != hipSuccess)
             return hip_fail(e, "block statistics");
         if ((e = launch_predict_quant(at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t), at<double>(ws, w.sim_q),
                                       at<double>(ws, w.sim_k), K, s, t, th, sm_scale, causal, mask,
                                       q8 ? at<int8_t>(ws, w.Kq) : nullptr, at<float>(ws, w.k_scale), st)) != hipSuccess)
             return hip_fail(e, "predict");
-        return timed_attn(Qa, Ka, qsc, ksc, at<char>(ws, w.v_tiles), s, mask, lam, sm_scale, causal, O, stats, queue, st);
+        return timed_attn(Qa, Ka, qsc, ksc, at<char>(ws, w.v_tiles), s, mask, lam, sm_scale, causal, O, stats, start, st);
     }
     std::lock_guard<std::mutex> lock(g_side_mutex);
     SideStream* side = side_stream();
@@ -527,14 +528,14 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
         if ((rc = run_stats_and_quant(Q, K, s, at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t),
                                       at<double>(ws, w.sim_q), at<double>(ws, w.sim_k), Qq, q_scale,
                                       q8 ? at<int8_t>(ws, w.Kq) : nullptr,
-                                      at<float>(ws, w.k_scale), at<float>(ws, w.k_mean), queue, st))) return rc;
+                                      at<float>(ws, w.k_scale), at<float>(ws, w.k_mean), start, st))) return rc;
         if ((rc = run_predict(s, ws, w, t, th, sm_scale, causal, mask, st))) return rc;
-        return run_attn(Qa, Ka, qsc, ksc, V, s, at<char>(ws, w.v_tiles), mask, lam, sm_scale, causal, O, stats, queue, st);
+        return run_attn(Qa, Ka, qsc, ksc, V, s, at<char>(ws, w.v_tiles), mask, lam, sm_scale, causal, O, stats, start, st);
     }
     // caller's stream: block statistics (+ Q quantization) -> fork -> predictor -> join -> attention
     // second stream:                                  fork -> V tiles, K mean, K quantization -> join
     if ((e = launch_block_stats(Q, K, s, at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t), at<double>(ws, w.sim_q),
-                                at<double>(ws, w.sim_k), Qq, q_scale, queue, st)) != hipSuccess)
+                                at<double>(ws, w.sim_k), Qq, q_scale, start, st)) != hipSuccess)
         return hip_fail(e, "block statistics");
     if ((e = hipEventRecord(side->fork, st)) != hipSuccess) return hip_fail(e, "record fork");
     if ((e = hipStreamWaitEvent(side->stream, side->fork, 0)) != hipSuccess) return hip_fail(e, "wait fork");
@@ -554,7 +555,7 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
     if ((e = hipStreamWaitEvent(st, side->join, 0)) != hipSuccess) return hip_fail(e, "wait join");
     if (rc_side) return rc_side;
     if (rc) return rc;
-    return timed_attn(Qa, Ka, qsc, ksc, at<char>(ws, w.v_tiles), s, mask, lam, sm_scale, causal, O, stats, queue, st);
+    return timed_attn(Qa, Ka, qsc, ksc, at<char>(ws, w.v_tiles), s, mask, lam, sm_scale, causal, O, stats, start, st);
 }
 
 int sparge_rel_l1(const void* O, const void* O_ref, const sparge_desc* desc, double* out, void* hip_stream) {
@@ -634,7 +635,7 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
     double* d_metrics = at<double>(ws, t.metrics);
     uint64_t* d_stats = at<uint64_t>(ws, t.stats);
     hipError_t e;
-    AttnQueue queue;
+    AttnStart start;
 
     // per input, once: block statistics, quantization, V tiles, and the full attention it is measured against
     HeadParams off;
@@ -645,11 +646,11 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
         if ((rc = run_stats_and_quant(Q[n], K[n], s, at<double>(f, w.pooled_q), at<double>(f, w.ksum_t),
                                       at<double>(f, w.sim_q), at<double>(f, w.sim_k), at<int8_t>(f, w.Qq),
                                       at<float>(f, w.q_scale), at<int8_t>(f, w.Kq), at<float>(f, w.k_scale),
-                                      at<float>(f, w.k_mean), AttnQueue{}, st))) return rc;
-        if ((rc = set_queue_for(s, at<unsigned int>(f, w.queue), &queue, st))) return rc;
+                                      at<float>(f, w.k_mean), AttnStart{}, st))) return rc;
+        if ((rc = plan_and_set_attn(s, at<void>(f, w.queue), nullptr, &start, st))) return rc;
         if ((rc = run_attn(at<int8_t>(f, w.Qq), at<int8_t>(f, w.Kq), at<float>(f, w.q_scale), at<float>(f, w.k_scale),
                            V[n], s, at<char>(f, w.v_tiles), nullptr, off, sm_scale, causal, o_ref(n), nullptr,
-                           queue, st)))
+                           start, st)))
             return rc;
     }
 
@@ -662,10 +663,10 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
             void* f = fwd(n);
             int r;
             if ((r = run_predict(s, f, w, tp, thp, sm_scale, causal, at<uint8_t>(f, w.mask), st))) return r;
-            if ((r = set_queue_for(s, at<unsigned int>(f, w.queue), &queue, st))) return r;
+            if ((r = plan_and_set_attn(s, at<void>(f, w.queue), d_stats, &start, st))) return r;
             if ((r = timed_attn(at<int8_t>(f, w.Qq), at<int8_t>(f, w.Kq), at<float>(f, w.q_scale),
                                 at<float>(f, w.k_scale), at<char>(f, w.v_tiles), s, at<uint8_t>(f, w.mask), lp,
-                                sm_scale, causal, o_cur, d_stats, queue, st))) return r;
+                                sm_scale, causal, o_cur, d_stats, start, st))) return r;
             if ((e = launch_rel_l1(o_cur, o_ref(n), s, d_metrics, st)) != hipSuccess) return hip_fail(e, "rel_l1");
             if ((e = hipMemcpyAsync(h_metrics.data(), d_metrics, BH * 2 * sizeof(double), hipMemcpyDeviceToHost, st)) != hipSuccess)
                 return hip_fail(e, "copy error sums");

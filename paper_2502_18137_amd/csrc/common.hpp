@@ -113,26 +113,32 @@ __host__ __device__ inline int range_item(int r0, int len, int p, int Tm, bool c
     return -1;  // p >= len
 }
 
-// Item counters of the attention kernel's work distribution: one per XCD range, 128 bytes apart, set to `start`
-// (the items of each range that the launch's workgroups take without asking) before the launch.  counters null:
-// every item has a workgroup of its own.
+// What has to be set before an attention launch, by whatever kernel of the call runs earlier (a kernel of its own
+// costs 5 us of a call): the item counters of its work distribution, one per XCD range, 128 bytes apart, to `start`
+// (the items of each range that the launch's workgroups take without asking; counters null: every item has a
+// workgroup of its own), and the caller's n_stats execution counters to zero (stats null: none).
 constexpr int QUEUE_PITCH = 32;
 constexpr size_t ATTN_QUEUE_BYTES = 1024;
 static_assert(8 * QUEUE_PITCH * sizeof(unsigned int) == ATTN_QUEUE_BYTES, "eight counters, 128 bytes apart");
-struct AttnQueue {
+struct AttnStart {
     unsigned int* counters;
     unsigned int start;
+    int n_stats;
+    unsigned long long* stats;
 };
-__device__ __forceinline__ void set_queue(const AttnQueue& q) {
-    if (q.counters && threadIdx.x < 8) q.counters[threadIdx.x * QUEUE_PITCH] = q.start;
+// (called by all threads of one workgroup)
+__device__ __forceinline__ void set_start(const AttnStart& a) {
+    if (a.counters && threadIdx.x < 8) a.counters[threadIdx.x * QUEUE_PITCH] = a.start;
+    if (a.stats)
+        for (int n = threadIdx.x; n < a.n_stats; n += blockDim.x) a.stats[n] = 0ull;
 }
 
 // ---- kernel launchers (host functions defined next to their kernels) ----------------------------
 // Block statistics of Q and K: pooled means of Q (+ its INT8 quantization if Qq), per-block channel sums of K (transposed
-// [B,H,d,Tn]), self-similarities; the item counters of the attention launch to come if queue has any.  sim_q null: only
+// [B,H,d,Tn]), self-similarities; and what `start` asks for.  sim_q null: only
 // what the quantization of Q and the mean of K need (Qq, q_scale, ksum_t).
 hipError_t launch_block_stats(const void* Q, const void* K, const Shape& s, double* pooled_q, double* ksum_t,
-                              double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, AttnQueue queue, hipStream_t st);
+                              double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, AttnStart start, hipStream_t st);
 // Short calls take the block statistics (and V tiles) in one launch and the predictor with the K quantization in
 // another.  Up to 256 key blocks (a row's logits fit the LDS of a workgroup of 8 rows at full occupancy) and as many
 // elements per tensor as below: a launch, an event and a wait saved are then worth more than what the passes lose in one
@@ -145,7 +151,7 @@ inline bool short_call(const Shape& s) {
 }
 // Short calls: all of launch_block_stats in one launch, with V re-tiled as launch_v_tiles does if v_tiles.
 hipError_t launch_prep(const void* Q, const void* K, const void* V, const Shape& s, double* pooled_q, double* ksum_t,
-                       double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, uint16_t* v_tiles, AttnQueue queue,
+                       double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, uint16_t* v_tiles, AttnStart start,
                        hipStream_t st);
 // Token mean of K per (b,h) from the block sums.
 hipError_t launch_k_mean(const double* ksum_t, const Shape& s, float* k_mean, hipStream_t st);
@@ -167,17 +173,15 @@ hipError_t launch_predict_quant(const double* pooled_q, const double* ksum_t, co
 hipError_t launch_v_tiles(const void* V, const Shape& s, uint16_t* v_tiles, hipStream_t st);
 // lut[b,h,i,:] = the j with mask[b,h,i,j] != 0, ascending, then -1; lut_count[b,h,i] = how many.
 hipError_t launch_mask_lut(const uint8_t* mask, const Shape& s, int32_t* lut, int32_t* lut_count, hipStream_t st);
-// stats[0..n) = 0 (a fill kernel, not a memset node, so callers may capture it in a graph).
-hipError_t launch_zero_stats(unsigned long long* stats, int n, hipStream_t st);
-// The item counters an attention launch of this shape needs, in ATTN_QUEUE_BYTES of device memory at `memory` that no
-// other launch may use at the same time; they have to be set (launch_prep, launch_set_queue) before the launch.
-hipError_t plan_queue(const Shape& s, unsigned int* memory, AttnQueue* queue);
-hipError_t launch_set_queue(const AttnQueue& queue, hipStream_t st);
+// What an attention launch of this shape needs set, with its counters in ATTN_QUEUE_BYTES of device memory at `memory`
+// that no other launch may use at the same time; launch_set_start sets it where no other kernel does.
+hipError_t plan_start(const Shape& s, unsigned int* memory, unsigned long long* stats, AttnStart* start);
+hipError_t launch_set_start(const AttnStart& start, hipStream_t st);
 // The sparse flash loop (accumulates into stats).
 hipError_t launch_attn(const void* Qp, const void* Kp, const float* q_scale, const float* k_scale,
                        const void* v_tiles, const float* v_scale, const Shape& s, const uint8_t* mask,
                        const HeadParams& lambda, float sm_scale, int causal, void* O, unsigned long long* stats,
-                       const AttnQueue& queue, hipStream_t st);
+                       const AttnStart& start, hipStream_t st);
 // FP8 form of V: per-(b,h,channel) |V| maxima (as fp32 bit patterns, zeroed here), scales amax/448, and
 // E4M3 tiles in the operand order of the 32x32x64 MFMA.
 hipError_t launch_v_tiles_fp8(const void* V, const Shape& s, unsigned char* tiles, float* v_scale,

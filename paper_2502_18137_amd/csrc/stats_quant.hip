@@ -296,10 +296,10 @@ template <int D, int DT, int ROWS, bool KSIDE, bool QUANT, bool STATS>
 __global__ __launch_bounds__(256) void block_stats_kernel(const uint16_t* __restrict__ X, Shape s,
                                                           double* __restrict__ pooled, double* __restrict__ sim,
                                                           int8_t* __restrict__ Xq, float* __restrict__ scale,
-                                                          AttnQueue queue) {
+                                                          AttnStart start) {
     __shared__ StatsLds<D> lds;
     int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    if (t + h + b == 0) set_queue(queue);
+    if (t + h + b == 0) set_start(start);
     if constexpr (KSIDE) {
         const int id = k_block_of((b * s.H + h) * s.Tn + t, s.B * s.H * s.Tn);
         t = id % s.Tn, h = id / s.Tn % s.H, b = id / s.Tn / s.H;
@@ -317,14 +317,14 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
                                                    double* __restrict__ pooled_q, double* __restrict__ ksum_t,
                                                    double* __restrict__ sim_q, double* __restrict__ sim_k,
                                                    int8_t* __restrict__ Qq, float* __restrict__ q_scale,
-                                                   uint16_t* __restrict__ v_tiles, AttnQueue queue) {
+                                                   uint16_t* __restrict__ v_tiles, AttnStart start) {
     __shared__ __align__(16) union {
         StatsLds<D> stats;
         VTileLds<D> tile;
     } lds;
     const int nq = s.B * s.H * s.Tm, nk = s.B * s.H * s.Tn;
     int id = blockIdx.x;
-    if (id == 0) set_queue(queue);
+    if (id == 0) set_start(start);
     auto at = [&](const uint16_t* X, int bh) { return X + (bh / s.H) * s.sb + (bh % s.H) * s.sh; };
     if (id < nq) {
         const int bh = id / s.Tm;
@@ -353,21 +353,21 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
     else return hipErrorInvalidValue;
 
 hipError_t launch_block_stats(const void* Q, const void* K, const Shape& s, double* pooled_q, double* ksum_t,
-                              double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, AttnQueue queue, hipStream_t st) {
+                              double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, AttnStart start, hipStream_t st) {
     const dim3 gq(s.Tm, s.H, s.B), gk(s.Tn, s.H, s.B);
     const uint16_t *q = static_cast<const uint16_t*>(Q), *k = static_cast<const uint16_t*>(K);
-    const AttnQueue none{};
+    const AttnStart none{};
 #define CALL(D, DT)                                                                                                   \
     if (!sim_q) {                                                                                                     \
         hipLaunchKernelGGL((block_stats_kernel<D, DT, BQ, false, true, false>), gq, dim3(256), 0, st, q, s, pooled_q, \
-                           sim_q, Qq, q_scale, queue);                                                                \
+                           sim_q, Qq, q_scale, start);                                                                \
         hipLaunchKernelGGL((block_stats_kernel<D, DT, BK, true, false, false>), gk, dim3(256), 0, st, k, s, ksum_t,   \
                            sim_k, (int8_t*)nullptr, (float*)nullptr, none);                                           \
     } else {                                                                                                          \
         if (Qq) hipLaunchKernelGGL((block_stats_kernel<D, DT, BQ, false, true, true>), gq, dim3(256), 0, st, q, s,    \
-                                   pooled_q, sim_q, Qq, q_scale, queue);                                              \
+                                   pooled_q, sim_q, Qq, q_scale, start);                                              \
         else hipLaunchKernelGGL((block_stats_kernel<D, DT, BQ, false, false, true>), gq, dim3(256), 0, st, q, s,      \
-                                pooled_q, sim_q, Qq, q_scale, queue);                                                 \
+                                pooled_q, sim_q, Qq, q_scale, start);                                                 \
         hipLaunchKernelGGL((block_stats_kernel<D, DT, BK, true, false, true>), gk, dim3(256), 0, st, k, s, ksum_t,    \
                            sim_k, (int8_t*)nullptr, (float*)nullptr, none);                                           \
     }
@@ -377,7 +377,7 @@ hipError_t launch_block_stats(const void* Q, const void* K, const Shape& s, doub
 }
 
 hipError_t launch_prep(const void* Q, const void* K, const void* V, const Shape& s, double* pooled_q, double* ksum_t,
-                       double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, uint16_t* v_tiles, AttnQueue queue,
+                       double* sim_q, double* sim_k, int8_t* Qq, float* q_scale, uint16_t* v_tiles, AttnStart start,
                        hipStream_t st) {
     if (!short_call(s)) return hipErrorInvalidValue;
     const dim3 grid(s.B * s.H * (s.Tm + (v_tiles ? 2 : 1) * s.Tn));
@@ -385,9 +385,9 @@ hipError_t launch_prep(const void* Q, const void* K, const void* V, const Shape&
                    *v = static_cast<const uint16_t*>(V);
 #define CALL(D, DT)                                                                                                  \
     if (Qq) hipLaunchKernelGGL((prep_kernel<D, DT, true>), grid, dim3(256), 0, st, q, k, v, s, pooled_q, ksum_t,     \
-                               sim_q, sim_k, Qq, q_scale, v_tiles, queue);                                           \
+                               sim_q, sim_k, Qq, q_scale, v_tiles, start);                                           \
     else hipLaunchKernelGGL((prep_kernel<D, DT, false>), grid, dim3(256), 0, st, q, k, v, s, pooled_q, ksum_t,       \
-                            sim_q, sim_k, Qq, q_scale, v_tiles, queue);
+                            sim_q, sim_k, Qq, q_scale, v_tiles, start);
     SPARGE_DISPATCH_D_DT(s, CALL)
 #undef CALL
     return hipGetLastError();
