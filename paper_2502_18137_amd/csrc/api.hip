@@ -632,8 +632,6 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
     auto fwd = [&](int n) { return static_cast<void*>(static_cast<char*>(ws) + t.per_input * n); };
     auto o_ref = [&](int n) { return static_cast<void*>(static_cast<char*>(ws) + t.per_input * n + t.fwd_bytes); };
     void* o_cur = at<char>(ws, t.o_cur);
-    double* d_metrics = at<double>(ws, t.metrics);
-    uint64_t* d_stats = at<uint64_t>(ws, t.stats);
     hipError_t e;
     AttnStart start;
 
@@ -652,58 +650,83 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
                            V[n], s, at<char>(f, w.v_tiles), nullptr, off, sm_scale, causal, o_ref(n), nullptr,
                            start, st)))
             return rc;
+        // the compressed logits are the same for every setting
+        if ((e = launch_logits(at<double>(f, w.pooled_q), at<double>(f, w.ksum_t), s, sm_scale, at<double>(f, w.logits), st)) !=
+            hipSuccess) return hip_fail(e, "logits");
     }
 
-    std::vector<double> h_metrics(BH * 2);
-    std::vector<uint64_t> h_stats(BH * 4);
-    // one setting on every input: per head the mean sparsity and the worst relative L1
-    auto evaluate = [&](const HeadParams& tp, const HeadParams& thp, const HeadParams& lp, double* sp, double* err) -> int {
-        for (int h = 0; h < H; ++h) { sp[h] = 0.0; err[h] = 0.0; }
+    // Settings are enqueued one after the other and read back together: each writes its error sums {2 doubles} and
+    // counters {4 uint64} per (batch, head) into a slot of its input, and the host waits once per batch of slots.  The
+    // slots lie where the K mean was (d floats per (batch, head)), which nothing reads after the quantization.
+    const size_t slot_bytes = (size_t)BH * (2 * sizeof(double) + 4 * sizeof(uint64_t));
+    const int batch = static_cast<int>((size_t)BH * s.d * sizeof(float) / slot_bytes);   // 5 (d = 64) or 10 (d = 128)
+    auto slot = [&](int n, int k) { return at<char>(fwd(n), w.k_mean) + k * slot_bytes; };
+    auto enqueue = [&](const HeadParams& tp, const HeadParams& thp, const HeadParams& lp, int k) -> int {
         for (int n = 0; n < n_inputs; ++n) {
             void* f = fwd(n);
+            double* sums = reinterpret_cast<double*>(slot(n, k));
+            uint64_t* counters = reinterpret_cast<uint64_t*>(sums + 2 * BH);
             int r;
-            if ((r = run_predict(s, f, w, tp, thp, sm_scale, causal, at<uint8_t>(f, w.mask), st))) return r;
-            if ((r = plan_and_set_attn(s, at<void>(f, w.queue), d_stats, &start, st))) return r;
+            if ((e = launch_topcdf(at<double>(f, w.logits), at<double>(f, w.sim_q), at<double>(f, w.sim_k), s, tp, thp, causal,
+                                   at<uint8_t>(f, w.mask), st)) != hipSuccess) return hip_fail(e, "topcdf");
+            if ((r = plan_and_set_attn(s, at<void>(f, w.queue), counters, &start, st))) return r;
             if ((r = timed_attn(at<int8_t>(f, w.Qq), at<int8_t>(f, w.Kq), at<float>(f, w.q_scale),
                                 at<float>(f, w.k_scale), at<char>(f, w.v_tiles), s, at<uint8_t>(f, w.mask), lp,
-                                sm_scale, causal, o_cur, d_stats, start, st))) return r;
-            if ((e = launch_rel_l1(o_cur, o_ref(n), s, d_metrics, st)) != hipSuccess) return hip_fail(e, "rel_l1");
-            if ((e = hipMemcpyAsync(h_metrics.data(), d_metrics, BH * 2 * sizeof(double), hipMemcpyDeviceToHost, st)) != hipSuccess)
-                return hip_fail(e, "copy error sums");
-            if ((e = hipMemcpyAsync(h_stats.data(), d_stats, BH * 4 * sizeof(uint64_t), hipMemcpyDeviceToHost, st)) != hipSuccess)
-                return hip_fail(e, "copy counters");
-            if ((e = hipStreamSynchronize(st)) != hipSuccess) return hip_fail(e, "synchronize");
-            for (int h = 0; h < H; ++h) {
-                double num = 0.0, den = 0.0;
-                uint64_t c[4] = {0, 0, 0, 0};
-                for (int b = 0; b < s.B; ++b) {
-                    num += h_metrics[(b * H + h) * 2 + 0];
-                    den += h_metrics[(b * H + h) * 2 + 1];
-                    for (int q = 0; q < 4; ++q) c[q] += h_stats[(b * H + h) * 4 + q];
-                }
-                sp[h] += 1.0 - 0.5 * ((double)c[0] / (double)c[2] + (double)c[1] / (double)c[3]);
-                err[h] = std::fmax(err[h], num / den);
-            }
+                                sm_scale, causal, o_cur, counters, start, st))) return r;
+            if ((e = launch_rel_l1(o_cur, o_ref(n), s, sums, st)) != hipSuccess) return hip_fail(e, "rel_l1");
         }
-        for (int h = 0; h < H; ++h) sp[h] /= n_inputs;
+        return SPARGE_OK;
+    };
+    // the first k_n slots of every input -> per setting and head the mean sparsity and the worst relative L1
+    std::vector<char> host(slot_bytes * std::min(batch, std::max(n_tau * n_theta, n_lambda)) * n_inputs);
+    auto collect = [&](int k_n, double* sp_err) -> int {
+        const size_t bytes = slot_bytes * k_n;
+        for (int n = 0; n < n_inputs; ++n)
+            if ((e = hipMemcpyAsync(host.data() + n * bytes, slot(n, 0), bytes, hipMemcpyDeviceToHost, st)) != hipSuccess)
+                return hip_fail(e, "copy error sums and counters");
+        if ((e = hipStreamSynchronize(st)) != hipSuccess) return hip_fail(e, "synchronize");
+        for (int k = 0; k < k_n; ++k)
+            for (int h = 0; h < H; ++h) {
+                double sp = 0.0, err = 0.0;
+                for (int n = 0; n < n_inputs; ++n) {
+                    const char* base = host.data() + n * bytes + k * slot_bytes;
+                    double num = 0.0, den = 0.0;
+                    uint64_t c[4] = {0, 0, 0, 0};
+                    for (int b = 0; b < s.B; ++b) {
+                        double m[2];
+                        uint64_t x[4];
+                        std::memcpy(m, base + (size_t)(b * H + h) * sizeof(m), sizeof(m));
+                        std::memcpy(x, base + (size_t)BH * sizeof(m) + (size_t)(b * H + h) * sizeof(x), sizeof(x));
+                        num += m[0];
+                        den += m[1];
+                        for (int q = 0; q < 4; ++q) c[q] += x[q];
+                    }
+                    sp += 1.0 - 0.5 * ((double)c[0] / (double)c[2] + (double)c[1] / (double)c[3]);
+                    err = std::fmax(err, num / den);
+                }
+                sp_err[((size_t)k * H + h) * 2 + 0] = sp / n_inputs;
+                sp_err[((size_t)k * H + h) * 2 + 1] = err;
+            }
         return SPARGE_OK;
     };
 
     // stage 1: the (tau, theta) grid with the lambda test off
     const int n1 = n_tau * n_theta;
-    std::vector<double> t1((size_t)n1 * H * 2), sp(H), err(H);
+    std::vector<double> t1((size_t)n1 * H * 2);
     HeadParams tp, thp, lp;
     std::memset(&tp, 0, sizeof(tp));
     std::memset(&thp, 0, sizeof(thp));
-    for (int a = 0; a < n_tau; ++a)
-        for (int b = 0; b < n_theta; ++b) {
-            for (int h = 0; h < H; ++h) { tp.v[h] = tau_grid[a]; thp.v[h] = theta_grid[b]; }
-            if ((rc = evaluate(tp, thp, off, sp.data(), err.data()))) return rc;
+    for (int k0 = 0; k0 < n1; k0 += batch) {
+        const int k_n = std::min(batch, n1 - k0);
+        for (int k = 0; k < k_n; ++k) {
             for (int h = 0; h < H; ++h) {
-                t1[((size_t)(a * n_theta + b) * H + h) * 2 + 0] = sp[h];
-                t1[((size_t)(a * n_theta + b) * H + h) * 2 + 1] = err[h];
+                tp.v[h] = tau_grid[(k0 + k) / n_theta];
+                thp.v[h] = theta_grid[(k0 + k) % n_theta];
             }
+            if ((rc = enqueue(tp, thp, off, k))) return rc;
         }
+        if ((rc = collect(k_n, &t1[(size_t)k0 * H * 2]))) return rc;
+    }
     std::vector<double> best_sp(H), best_err(H);
     for (int h = 0; h < H; ++h) {
         int best = -1;
@@ -728,18 +751,25 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
 
     // stage 2: the lambda grid at each head's own (tau, theta)
     std::memset(&lp, 0, sizeof(lp));
-    for (int c = 0; c < n_lambda; ++c) {
-        for (int h = 0; h < H; ++h) lp.v[h] = lambda_grid[c];
-        if ((rc = evaluate(tp, thp, lp, sp.data(), err.data()))) return rc;
+    std::vector<double> t2((size_t)n_lambda * H * 2);
+    for (int c0 = 0; c0 < n_lambda; c0 += batch) {
+        const int k_n = std::min(batch, n_lambda - c0);
+        for (int k = 0; k < k_n; ++k) {
+            for (int h = 0; h < H; ++h) lp.v[h] = lambda_grid[c0 + k];
+            if ((rc = enqueue(tp, thp, lp, k))) return rc;
+        }
+        if ((rc = collect(k_n, &t2[(size_t)c0 * H * 2]))) return rc;
+    }
+    if (stage2 && n_lambda) std::memcpy(stage2, t2.data(), t2.size() * sizeof(double));
+    for (int c = 0; c < n_lambda; ++c)
         for (int h = 0; h < H; ++h) {
-            if (stage2) { stage2[((size_t)c * H + h) * 2] = sp[h]; stage2[((size_t)c * H + h) * 2 + 1] = err[h]; }
-            if (err[h] < (double)l2 && sp[h] > best_sp[h]) {
+            const double c_sp = t2[((size_t)c * H + h) * 2], c_err = t2[((size_t)c * H + h) * 2 + 1];
+            if (c_err < (double)l2 && c_sp > best_sp[h]) {
                 lambda[h] = lambda_grid[c];
-                best_sp[h] = sp[h];
-                best_err[h] = err[h];
+                best_sp[h] = c_sp;
+                best_err[h] = c_err;
             }
         }
-    }
     for (int h = 0; h < H; ++h) {
         if (sparsity) sparsity[h] = best_sp[h];
         if (l1_out) l1_out[h] = best_err[h];
