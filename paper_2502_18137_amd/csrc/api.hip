@@ -239,7 +239,7 @@ int run_stats_and_quant(const void* Q, const void* K, const Shape& s, double* po
 int run_predict(const Shape& s, void* ws, const Workspace& w, const HeadParams& tau, const HeadParams& theta,
                 float sm_scale, int causal, uint8_t* mask, hipStream_t st) {
     hipError_t e;
-    if ((e = launch_logits(at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t), s, sm_scale,
+    if ((e = launch_logits(at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t), s, sm_scale, causal,
                            at<double>(ws, w.logits), st)) != hipSuccess) return hip_fail(e, "logits");
     if ((e = launch_topcdf(at<double>(ws, w.logits), at<double>(ws, w.sim_q), at<double>(ws, w.sim_k), s, tau,
                            theta, causal, mask, st)) != hipSuccess) return hip_fail(e, "topcdf");
@@ -651,7 +651,8 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
                            start, st)))
             return rc;
         // the compressed logits are the same for every setting
-        if ((e = launch_logits(at<double>(f, w.pooled_q), at<double>(f, w.ksum_t), s, sm_scale, at<double>(f, w.logits), st)) !=
+        if ((e = launch_logits(at<double>(f, w.pooled_q), at<double>(f, w.ksum_t), s, sm_scale, causal, at<double>(f, w.logits),
+                               st)) !=
             hipSuccess) return hip_fail(e, "logits");
     }
 

@@ -158,8 +158,8 @@ hipError_t launch_k_mean(const double* ksum_t, const Shape& s, float* k_mean, hi
 // INT8 quantization of K - k_mean.
 hipError_t launch_quant_k(const void* K, const Shape& s, const float* k_mean, int8_t* Kq, float* k_scale,
                           hipStream_t st);
-// Compressed logits S_hat = sm_scale * q k^T (no masking), fp64 [B,H,Tm,Tn].
-hipError_t launch_logits(const double* pooled_q, const double* ksum_t, const Shape& s, float sm_scale,
+// Compressed logits S_hat = sm_scale * q k^T, fp64 [B,H,Tm,Tn]; causal: only tiles that some row sees are written.
+hipError_t launch_logits(const double* pooled_q, const double* ksum_t, const Shape& s, float sm_scale, int causal,
                          double* logits, hipStream_t st);
 // Softmax + TopCdf + overrides per mask row.
 hipError_t launch_topcdf(const double* logits, const double* sim_q, const double* sim_k, const Shape& s,

@@ -23,6 +23,12 @@ __device__ __forceinline__ double shfl_up_f64(double v, int delta) {
     return __hiloint2double(hi, lo);
 }
 
+// Key blocks that mask row i has to rank: all of them, or (causal) those up to the end of its own Q block.
+__device__ __forceinline__ int visible_blocks(const Shape& s, int i, int causal) {
+    static_assert(BQ == 2 * BK, "a Q block ends with the second key block of its own");
+    return causal ? min(s.Tn, 2 * i + 2) : s.Tn;
+}
+
 // Compressed logits as an fp64 matrix product on the matrix cores: a wave computes RT x 16 pooled query rows x 64
 // key blocks with v_mfma_f64_16x16x4_f64 (operands: lane = row or column + 16 * k; result register r of a
 // lane = row 4 r + lane / 16, column lane % 16).  The pooled queries are row-major, the key sums
@@ -33,11 +39,11 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 template <int D, int RT>
 __global__ __launch_bounds__(256) void logits_kernel(const double* __restrict__ pooled_q,
                                                       const double* __restrict__ ksum_t, Shape s,
-                                                      double sm_scale, double* __restrict__ logits) {
+                                                      double sm_scale, int causal, double* __restrict__ logits) {
     const long long bh = blockIdx.z;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int i0 = (blockIdx.y * 4 + wave) * 16 * RT, j0 = blockIdx.x * 64;
-    if (i0 >= s.Tm) return;
+    if (i0 >= s.Tm || j0 >= visible_blocks(s, i0 + 16 * RT - 1, causal)) return;   // (nobody reads what no row sees)
     const int l16 = lane & 15, kk = lane >> 4;
     const double* qrow[RT];
 #pragma unroll
@@ -128,10 +134,9 @@ __global__ __launch_bounds__(256) void topcdf_kernel(const double* __restrict__ 
     double mx = NEG;
     for (int j = tid; j < npad; j += 256) {
         double x = NEG;
-        if (j < s.Tn) {
+        if (j < visible_blocks(s, i, causal)) {
             x = row[j];
             if (sk[j] < theta) x = NEG;
-            if (causal && j * BK > i * BQ + (BQ - 1)) x = NEG;
         }
         keys[j] = x;
         mx = fmax(mx, x);
@@ -386,15 +391,17 @@ __device__ __forceinline__ double wave_max(double v) {
 // below EPL exchanges inside a lane (compile-time register indices), a larger one takes the partner
 // lane's key with DPP moves or lane swaps (vector ALU: with ds_bpermute the LDS pipeline was the limit);
 // nothing but the final flags and the exact probabilities goes through LDS, and no workgroup barrier is needed.  Same comparisons, hence the same order, as the LDS version.
-// row_at(j): the row's logit of key block j; pval, flag: 64 * EPL entries of LDS of this wave's own (pval may be
+// The ranks cover the n key blocks that the row sees (n <= 64 EPL); the others are 0 in the mask.
+// row_at(j): the row's logit of key block j < n; pval, flag: 64 * EPL entries of LDS of this wave's own (pval may be
 // where row_at reads from: all logits are read before the first probability is written).
 template <int EPL, class RowAt>
 __device__ __forceinline__ void topcdf_row(RowAt row_at, const int i, const double sim_q_i, const double* __restrict__ sk,
                                            const Shape& s, const double tau, const double theta, const int causal,
-                                           const int lane, double* pval, uint8_t* flag, uint8_t* __restrict__ out) {
+                                           const int n, const int lane, double* pval, uint8_t* flag,
+                                           uint8_t* __restrict__ out) {
     const double NEG = -__builtin_inf();
     if (sim_q_i < theta) {   // a query block that is not self-similar keeps every visible key block
-        for (int j = lane; j < s.Tn; j += 64) out[j] = (causal && j * BK > i * BQ + (BQ - 1)) ? 0 : 1;
+        for (int j = lane; j < s.Tn; j += 64) out[j] = j < n ? 1 : 0;
         return;
     }
     // 1.-2. masked logits, softmax, probabilities (entries lane * EPL + e: a lane reads one contiguous piece)
@@ -404,10 +411,9 @@ __device__ __forceinline__ void topcdf_row(RowAt row_at, const int i, const doub
     for (int e = 0; e < EPL; ++e) {
         const int j = lane * EPL + e;
         x[e] = NEG;
-        if (j < s.Tn) {
+        if (j < n) {
             x[e] = row_at(j);
             if (sk[j] < theta) x[e] = NEG;
-            if (causal && j * BK > i * BQ + (BQ - 1)) x[e] = NEG;
         }
         mx = fmax(mx, x[e]);
     }
@@ -427,11 +433,11 @@ __device__ __forceinline__ void topcdf_row(RowAt row_at, const int i, const doub
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
         const int j = lane * EPL + e;
-        const double p = j < s.Tn ? x[e] * rz : 0.0;
+        const double p = j < n ? x[e] * rz : 0.0;
         tot += p;
         pval[j] = p;
         flag[j] = 0;
-        key[e] = j < s.Tn ? ((static_cast<unsigned long long>(__double_as_longlong(p)) & ~0xFFFFull) |
+        key[e] = j < n ? ((static_cast<unsigned long long>(__double_as_longlong(p)) & ~0xFFFFull) |
                              static_cast<unsigned long long>(0xFFFF - j))
                           : 0ull;   // padding ranks last
     }
@@ -465,14 +471,36 @@ __device__ __forceinline__ void topcdf_row(RowAt row_at, const int i, const doub
 
     // 5. fix-block overrides and causal rules, then the row goes out
     for (int j = lane; j < s.Tn; j += 64) {
-        uint8_t m = flag[j];
-        if (sk[j] < theta) m = 1;
-        if (causal) {
-            if (j * BK > i * BQ + (BQ - 1)) m = 0;
-            if (j == (i * BQ) / BK) m = 1;
+        uint8_t m = 0;
+        if (j < n) {
+            m = flag[j];
+            if (sk[j] < theta) m = 1;
+            if (causal && j == (i * BQ) / BK) m = 1;
         }
         out[j] = m;
     }
+}
+// The same with the fewest ranks per lane that hold the row: a causal row of a quarter (half) of the blocks sorts a
+// quarter (half) of the ranks in fewer stages.  Causal predictor call, with the logits tiles left out that no row sees:
+// 428 against 471 us at 32 x 65536 x 128, 365 against 423 us at 8 x 131072 x 128 (TopCdf at 32 x 32768: 75 against 108 us).
+template <int EPL, class RowAt>
+__device__ __forceinline__ void topcdf_row_of(RowAt row_at, const int i, const double sim_q_i, const double* __restrict__ sk,
+                                              const Shape& s, const double tau, const double theta, const int causal,
+                                              const int lane, double* pval, uint8_t* flag, uint8_t* __restrict__ out) {
+    const int n = visible_blocks(s, i, causal);
+    if constexpr (EPL >= 8) {
+        if (n <= 16 * EPL) {
+            topcdf_row<EPL / 4>(row_at, i, sim_q_i, sk, s, tau, theta, causal, n, lane, pval, flag, out);
+            return;
+        }
+    }
+    if constexpr (EPL >= 4) {
+        if (n <= 32 * EPL) {
+            topcdf_row<EPL / 2>(row_at, i, sim_q_i, sk, s, tau, theta, causal, n, lane, pval, flag, out);
+            return;
+        }
+    }
+    topcdf_row<EPL>(row_at, i, sim_q_i, sk, s, tau, theta, causal, n, lane, pval, flag, out);
 }
 
 // One mask row per wave, the logits from memory.
@@ -486,13 +514,13 @@ __global__ __launch_bounds__(256) void topcdf_wave_kernel(const double* __restri
     __shared__ double pval[4][NPAD];
     __shared__ uint8_t flag[4][NPAD];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int rowid = blockIdx.x * 4 + wave;          // (b, h, i) flattened
+    const int rowid = __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x) * 4 + wave);   // (b, h, i) flattened
     if (rowid >= n_rows) return;
     const int i = rowid % s.Tm;
     const long long bh = rowid / s.Tm;
     const int h = static_cast<int>(bh % s.H);
     const double* row = logits + (long long)rowid * s.Tn;
-    topcdf_row<EPL>([&](int j) { return row[j]; }, i, sim_q[rowid], sim_k + bh * s.Tn, s, static_cast<double>(tau_h.v[h]),
+    topcdf_row_of<EPL>([&](int j) { return row[j]; }, i, sim_q[rowid], sim_k + bh * s.Tn, s, static_cast<double>(tau_h.v[h]),
                     static_cast<double>(theta_h.v[h]), causal, lane, pval[wave], flag[wave],
                     mask + (long long)rowid * s.Tn);
 }
@@ -532,7 +560,7 @@ __global__ __launch_bounds__(64 * R) void predict_quant_kernel(
         const int i0 = id % groups * R, l16 = lane & 15, kk = lane >> 4;
         const double* qrow = pooled_q + (bh * s.Tm + min(i0 + l16, s.Tm - 1)) * D + kk;   // rows past Tm or R: not used
 #pragma unroll 1
-        for (int j0 = wave * 16; j0 < s.Tn; j0 += 16 * R) {
+        for (int j0 = wave * 16; j0 < visible_blocks(s, i0 + R - 1, causal); j0 += 16 * R) {
             const double* kcol = ksum_t + bh * D * s.Tn + (long long)kk * s.Tn + min(j0 + l16, s.Tn - 1);
             v4d acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -549,7 +577,7 @@ __global__ __launch_bounds__(64 * R) void predict_quant_kernel(
         const int i = i0 + wave, h = static_cast<int>(bh % s.H);
         if (i >= s.Tm) return;
         const double* row = lds.rows.lg[wave];
-        topcdf_row<EPL>([&](int j) { return row[j]; }, i, sim_q[bh * s.Tm + i], sim_k + bh * s.Tn, s,
+        topcdf_row_of<EPL>([&](int j) { return row[j]; }, i, sim_q[bh * s.Tm + i], sim_k + bh * s.Tn, s,
                         static_cast<double>(tau_h.v[h]), static_cast<double>(theta_h.v[h]), causal, lane,
                         lds.rows.lg[wave], lds.rows.flag[wave], mask + (bh * s.Tm + i) * s.Tn);
         return;
@@ -615,14 +643,14 @@ hipError_t launch_mask_lut(const uint8_t* mask, const Shape& s, int32_t* lut, in
     return hipGetLastError();
 }
 
-hipError_t launch_logits(const double* pooled_q, const double* ksum_t, const Shape& s, float sm_scale,
+hipError_t launch_logits(const double* pooled_q, const double* ksum_t, const Shape& s, float sm_scale, int causal,
                          double* logits, hipStream_t st) {
     // two row tiles of 16 pooled queries per wave where there are enough rows to fill the chip that way
     // (measured: 55 against 61 us at T_m = 360, 33 against 39 us at T_m = 256 with 32 heads; 18 against 17 us at T_m = 138)
     const int rt = s.Tm >= 192 ? 2 : 1;
     dim3 grid((s.Tn + 63) / 64, (s.Tm + 64 * rt - 1) / (64 * rt), s.B * s.H);
     const double scale = sm_scale > 0.f ? static_cast<double>(sm_scale) : 1.0 / sqrt(static_cast<double>(s.d));
-#define CALL(D, RT) hipLaunchKernelGGL((logits_kernel<D, RT>), grid, dim3(256), 0, st, pooled_q, ksum_t, s, scale, logits)
+#define CALL(D, RT) hipLaunchKernelGGL((logits_kernel<D, RT>), grid, dim3(256), 0, st, pooled_q, ksum_t, s, scale, causal, logits)
     if (s.d == 64) { if (rt == 2) CALL(64, 2); else CALL(64, 1); }
     else { if (rt == 2) CALL(128, 2); else CALL(128, 1); }
 #undef CALL
