@@ -1,6 +1,6 @@
 // C ABI of libsparge: argument validation, workspace partition, kernel sequencing.
 // Nothing here allocates device memory; every kernel goes onto the caller's stream, except that
-// sparge_forward runs three passes on a second stream between a fork and a join on the caller's.  Only
+// sparge_forward, beyond short calls, runs three passes on a second stream between a fork and a join on the caller's.  Only
 // sparge_tune synchronises (it decides on the host between candidates).
 #include <cmath>
 #include <cstdarg>
@@ -508,7 +508,10 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
     AttnStart start;
     hipError_t e;
     if ((rc = plan_attn(s, at<void>(ws, w.queue), stats, &start))) return rc;
+    std::unique_lock<std::mutex> lock(g_side_mutex);
+    SideStream* side = side_stream();   // short calls do not use it, but a first call of any length makes it
     if (short_call(s)) {
+        lock.unlock();
         // Three launches on the caller's stream: block statistics with the V tiles; predictor beside the K
         // quantization; attention.  (The FP8 tiles need V's maxima first: launches of their own.)
         if (s.pv_fp8 && (e = retile_v(V, s, at<char>(ws, w.v_tiles), st)) != hipSuccess) return hip_fail(e, "v_tiles");
@@ -522,8 +525,6 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
             return hip_fail(e, "predict");
         return timed_attn(Qa, Ka, qsc, ksc, at<char>(ws, w.v_tiles), s, mask, lam, sm_scale, causal, O, stats, start, st);
     }
-    std::lock_guard<std::mutex> lock(g_side_mutex);
-    SideStream* side = side_stream();
     if (!side) {
         if ((rc = run_stats_and_quant(Q, K, s, at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t),
                                       at<double>(ws, w.sim_q), at<double>(ws, w.sim_k), Qq, q_scale,

@@ -2,6 +2,7 @@
 //   logits : S_hat = sm_scale * q k^T on the pooled tokens, fp64 (tiny next to the attention itself)
 //   topcdf : per mask row: -inf columns, softmax, TopCdf(tau) by an in-LDS bitonic sort and a
 //            prefix sum, fix-block overrides, causal rules.
+//   short calls: both in one launch, beside the K quantization (predict_quant_kernel).
 // All arithmetic is fp64 so that block decisions agree with an fp64 reference except for
 // statistics that sit within ~1e-13 of a threshold.
 #include "lanes.hpp"
