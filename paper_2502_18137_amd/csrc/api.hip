@@ -401,6 +401,7 @@ int sparge_attn_quantized(const int8_t* Qq, const int8_t* Kq, const float* q_sca
     Shape s;
     int rc = check_desc(desc, &s);
     if (rc) return rc;
+    s.qk16 = 0;  // the operands are INT8 whatever qk_dtype says
     if (!Qq || !Kq || !q_scale || !k_scale || !V || !O) return fail(SPARGE_EINVAL, "NULL tensor argument");
     if (misaligned(Qq) || misaligned(Kq) || misaligned(V) || misaligned(O))
         return fail(SPARGE_EINVAL, "tensor pointers must be 16-byte aligned");
@@ -441,6 +442,7 @@ int sparge_attn_tiled(const int8_t* Qq, const int8_t* Kq, const float* q_scale, 
     Shape s;
     int rc = check_desc(desc, &s);
     if (rc) return rc;
+    s.qk16 = 0;  // the operands are INT8 whatever qk_dtype says
     if (!Qq || !Kq || !q_scale || !k_scale || !v_tiles || !O) return fail(SPARGE_EINVAL, "NULL tensor argument");
     if (misaligned(Qq) || misaligned(Kq) || misaligned(v_tiles) || misaligned(O))
         return fail(SPARGE_EINVAL, "tensor pointers must be 16-byte aligned");
@@ -608,6 +610,7 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
     Shape s;
     int rc = check_desc(desc, &s);
     if (rc) return rc;
+    s.qk16 = 0;  // the search quantizes and tunes the INT8 product
     if (n_inputs < 1 || !Q || !K || !V) return fail(SPARGE_EINVAL, "no inputs");
     if (n_tau < 1 || n_theta < 1 || n_lambda < 0 || !tau_grid || !theta_grid || (n_lambda && !lambda_grid))
         return fail(SPARGE_EINVAL, "empty tau/theta grid or missing lambda grid");

@@ -110,6 +110,31 @@ def test_qk16_unsupported_combinations_raise(sp):
         sp.sparge_attn(Q, K, V, None, -math.inf, qk16=True, pv_fp8=True)
 
 
+@pytest.mark.parametrize("N,d,causal", [(200, 64, False), (333, 128, True)])
+def test_entry_points_on_int8_operands_ignore_qk_dtype(sp, monkeypatch, N, d, causal):
+    """sparge.h: qk_dtype is read by sparge_attn and sparge_forward only.  With SPARGE_QK_16BIT in the descriptor the
+    entry points that take (or make) INT8 operands give the bits they give without it; what the descriptor may not
+    say together with it is refused by them as by all others."""
+    import torch
+    import paper_2502_18137_amd.binding as b
+    w = small_workload("desc", N=N, d=d, dtype="bf16", H=2, causal=causal, seed=17)
+    print(f"N={N} d={d} causal={causal}", flush=True)
+    x, Q, K, V = gpu_inputs(w)
+    ops, tiles = sp.sparge_quantize(Q, K)[:4], sp.sparge_v_tiles(V)
+    calls = {"attn_quantized": lambda: sp.sparge_attn_quantized(*ops, V, None, w.lam, causal=causal),
+             "attn_tiled": lambda: sp.sparge_attn_tiled(*ops, tiles, V, None, w.lam, causal=causal)}
+    search = lambda: sp.sparge_tune([(Q, K, V)], [0.7, 0.9], [0.4], [-5.0], 0.1, 0.12, causal=causal)
+    plain, plain_search = {n: f() for n, f in calls.items()}, search()
+    desc = b._desc
+    monkeypatch.setattr(b, "_desc", lambda x, pv_fp8=False, qk16=False: desc(x, pv_fp8, True))
+    for n, f in calls.items():
+        assert torch.equal(f(), plain[n]), n
+    flagged = search()
+    assert np.array_equal(flagged["stage1"], plain_search["stage1"]) and np.array_equal(flagged["stage2"], plain_search["stage2"])
+    with pytest.raises(sp.SpargeError, match="FP8"):
+        sp.sparge_attn_quantized(*ops, V, None, w.lam, causal=causal, pv_fp8=True)
+
+
 def test_qk16_video_configuration_sampled_rows(sp):
     """The N = 17550 video configuration in full (48 heads, one sparge_forward call) with the 16-bit Q K^T
     product: same mask as the INT8 path, counters against the mask, and the output rows of five Q blocks of two
