@@ -1,5 +1,6 @@
 """Item counts around the number of resident workgroups (two per compute unit): up to it every workgroup computes the
-one item at its own position and no counter is used, one item more and the counters start behind those positions.
+one item at its own position and no counter is used, one item more and the counters start behind those positions; with
+a few items per workgroup every workgroup draws from its own range first and from the other ranges once that is empty.
 Each (batch, head) must come out as in a call of its own (whose few items never need a counter), bit for bit, and
 the first and last ones as the oracle has them."""
 import numpy as np
@@ -12,7 +13,7 @@ from synth import make_workload
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("extra,d,causal", [(-1, 64, False), (0, 128, False), (1, 64, True), (9, 128, False)])
+@pytest.mark.parametrize("extra,d,causal", [(-1, 64, False), (0, 128, False), (1, 64, True), (9, 128, False), (1033, 64, False)])
 def test_items_around_the_resident_workgroups(extra, d, causal):
     import torch
     import paper_2502_18137_amd as sp
