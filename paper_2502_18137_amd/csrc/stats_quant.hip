@@ -299,7 +299,7 @@ __global__ __launch_bounds__(256) void block_stats_kernel(const uint16_t* __rest
                                                           AttnStart start) {
     __shared__ StatsLds<D> lds;
     int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    if (t + h + b == 0) set_start(start);
+    if (t + h + b == 0) set_start(start, 0, 1);
     if constexpr (KSIDE) {
         const int id = k_block_of((b * s.H + h) * s.Tn + t, s.B * s.H * s.Tn);
         t = id % s.Tn, h = id / s.Tn % s.H, b = id / s.Tn / s.H;
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
     } lds;
     const int nq = s.B * s.H * s.Tm, nk = s.B * s.H * s.Tn;
     int id = blockIdx.x;
-    if (id == 0) set_start(start);
+    if (id == 0) set_start(start, 0, 1);
     auto at = [&](const uint16_t* X, int bh) { return X + (bh / s.H) * s.sb + (bh % s.H) * s.sh; };
     if (id < nq) {
         const int bh = id / s.Tm;

@@ -36,3 +36,27 @@ def test_items_around_the_resident_workgroups(extra, d, causal):
         ref = so.sparse_attention(x["q"][0, g], x["k"][0, g], x["v"][0, g], None, lam=f32(lam), causal=causal,
                                   quant=True, pv_dtype="bf16", ref_slack=REF_SLACK)
         assert so.rel_l1(flat[g], so.round16(ref.O, "bf16")) <= 2e-3
+
+
+@pytest.mark.parametrize("B,H", [(1, 1), (1, 64), (5, 13), (3, 127)])
+def test_counters_are_set_whatever_they_held(B, H, monkeypatch):
+    """The execution counters come in uninitialised and are set by an earlier kernel of the call: block statistics (short
+    calls and others) or a kernel of its own, with a workgroup per 256 of them."""
+    import torch
+    import paper_2502_18137_amd as sp
+    g = torch.Generator(device="cuda").manual_seed(H)
+    Q, K, V = (torch.randn(B, H, 100, 64, generator=g, device="cuda").to(torch.bfloat16) for _ in range(3))
+    ops, tiles = sp.sparge_quantize(Q, K)[:4], sp.sparge_v_tiles(V)
+    empty = torch.empty
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: empty(*a, **k).fill_(-1) if k.get("dtype") == torch.int64 else empty(*a, **k))
+    want = torch.tensor([2, 8, 2, 8], device="cuda").expand(B, H, 4)     # one Q block of two key blocks, all executed
+    inf = float("inf")
+    tiled = torch.full((B, H, 4), -1, dtype=torch.int64, device="cuda")
+    sp.sparge_attn_tiled(*ops, tiles, V, None, -inf, stats=tiled)
+    for what, got in (("forward", sp.sparge_forward(Q, K, V, 1.0, 2.0, -inf, return_stats=True)[1]),
+                      ("attn", sp.sparge_attn(Q, K, V, None, -inf, return_stats=True)[1]),
+                      ("attn, 16-bit Q K^T", sp.sparge_attn(Q, K, V, None, -inf, return_stats=True, qk16=True)[1]),
+                      ("attn_quantized", sp.sparge_attn_quantized(*ops, V, None, -inf, return_stats=True)[1]),
+                      ("attn_tiled", tiled)):
+        print(f"B={B} H={H} {what}", flush=True)
+        assert torch.equal(got, want), what
