@@ -18,7 +18,6 @@ __global__ __launch_bounds__(1024) void rel_l1_kernel(const uint16_t* __restrict
     const long long base = b * s.sb + h * s.sh;
     const int col = threadIdx.x % CPR, r0 = threadIdx.x / CPR;
     double num = 0.0, den = 0.0;
-#pragma unroll 4   // (four rows' loads in flight; the order of the sums stays)
     for (int row = r0; row < s.N; row += RPI) {
         const long long off = base + (long long)row * s.sn + col * 8;
         const uint4 a = *reinterpret_cast<const uint4*>(O + off);
