@@ -105,19 +105,18 @@ struct Workspace {
 
 Workspace plan(const Shape& s, int entry) {
     const size_t BH = (size_t)s.B * s.H;
-    const bool stats = entry == SPARGE_WS_QUANTIZE || entry == SPARGE_WS_PREDICT || entry == SPARGE_WS_ATTN ||
-                       entry == SPARGE_WS_FORWARD;
     const bool pred = entry == SPARGE_WS_PREDICT || entry == SPARGE_WS_FORWARD;
     const bool quant_in_ws = entry == SPARGE_WS_ATTN || entry == SPARGE_WS_FORWARD;
+    const bool sums = pred || quant_in_ws || entry == SPARGE_WS_QUANTIZE;
     const bool attn = entry == SPARGE_WS_ATTN || entry == SPARGE_WS_ATTN_QUANTIZED || entry == SPARGE_WS_FORWARD;
     const bool loop = attn || entry == SPARGE_WS_ATTN_TILED;
     Workspace w{};
     size_t off = 0;
     auto take = [&](bool used, size_t bytes) { size_t o = off; if (used) off += align256(bytes); return o; };
-    w.pooled_q = take(stats, BH * s.Tm * s.d * sizeof(double));
-    w.ksum_t = take(stats, BH * s.Tn * s.d * sizeof(double));
-    w.sim_q = take(stats, BH * s.Tm * sizeof(double));
-    w.sim_k = take(stats, BH * s.Tn * sizeof(double));
+    w.pooled_q = take(pred, BH * s.Tm * s.d * sizeof(double));
+    w.ksum_t = take(sums, BH * s.Tn * s.d * sizeof(double));   // the quantization needs the mean of K from them
+    w.sim_q = take(pred, BH * s.Tm * sizeof(double));
+    w.sim_k = take(pred, BH * s.Tn * sizeof(double));
     w.k_mean = take(quant_in_ws, BH * s.d * sizeof(float));
     w.logits = take(pred, BH * s.Tm * s.Tn * sizeof(double));
     w.Qq = take(quant_in_ws, BH * s.N * s.d);
@@ -574,9 +573,9 @@ int sparge_rel_l1(const void* O, const void* O_ref, const sparge_desc* desc, dou
 namespace {
 
 // Workspace of the hyper-parameter search: per input a forward workspace and the full-attention output,
-// then one output buffer, the error sums and the counters.
+// then one output buffer.  (The error sums and counters lie inside the forward workspaces.)
 struct TuneWs {
-    size_t fwd_bytes, out_bytes, per_input, o_cur, metrics, stats, total;
+    size_t fwd_bytes, out_bytes, per_input, o_cur, total;
 };
 TuneWs tune_layout(const Shape& s, int n_inputs) {
     TuneWs t{};
@@ -585,9 +584,7 @@ TuneWs tune_layout(const Shape& s, int n_inputs) {
     t.out_bytes = align256(span * sizeof(uint16_t));
     t.per_input = t.fwd_bytes + t.out_bytes;
     t.o_cur = t.per_input * n_inputs;
-    t.metrics = t.o_cur + t.out_bytes;
-    t.stats = t.metrics + align256((size_t)s.B * s.H * 2 * sizeof(double));
-    t.total = t.stats + align256((size_t)s.B * s.H * 4 * sizeof(uint64_t));
+    t.total = t.o_cur + t.out_bytes;
     return t;
 }
 

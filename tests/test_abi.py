@@ -54,6 +54,34 @@ def test_argument_validation_needs_no_gpu():
     assert rc == -1
 
 
+@pytest.mark.parametrize("B,H,N,d", [(1, 2, 2048, 64), (3, 5, 1000, 128)])
+def test_workspaces_hold_what_their_entry_points_use(B, H, N, d):
+    """sparge_quantize and sparge_attn need K's block sums but no pooled Q and no similarities; the search needs per
+    input a forward workspace and an output, and one more output."""
+    import paper_2502_18137_amd as sp
+    from paper_2502_18137_amd.binding import _Desc
+    lib = sp.load_library()
+    desc = _Desc(B, H, N, d, 1, H * N * d, N * d, d)
+    def of(entry):
+        n = ctypes.c_size_t(0)
+        assert lib.sparge_workspace_bytes(ctypes.byref(desc), entry, ctypes.byref(n)) == 0
+        return n.value
+    up = lambda x: (x + 255) // 256 * 256
+    BH, Tm, Tn = B * H, -(-N // 128), -(-N // 64)
+    sums = up(BH * Tn * d * 8)
+    assert of(sp.WS_QUANTIZE) == sums
+    quant = up(BH * d * 4) + 2 * up(BH * N * d) + up(BH * Tm * 4) + up(BH * Tn * 4)
+    tail = up(BH * Tn * d * 64 * 2) + 1024                     # V tiles, item counters
+    assert of(sp.WS_ATTN) == sums + quant + tail
+    stats = up(BH * Tm * d * 8) + up(BH * Tm * 8) + up(BH * Tn * 8)
+    assert of(sp.WS_FORWARD) == sums + quant + tail + stats + up(BH * Tm * Tn * 8) + up(BH * Tm * Tn)
+    assert of(sp.WS_PREDICT) == sums + stats + up(BH * Tm * Tn * 8)
+    for inputs in (1, 3):
+        n = ctypes.c_size_t(0)
+        assert lib.sparge_tune_workspace_bytes(ctypes.byref(desc), inputs, ctypes.byref(n)) == 0
+        assert n.value == inputs * (of(sp.WS_FORWARD) + up(BH * N * d * 2)) + up(BH * N * d * 2)
+
+
 def test_missing_library_fails_loudly(monkeypatch):
     import paper_2502_18137_amd.binding as b
     monkeypatch.setattr(b, "_LIB", None)
