@@ -2,11 +2,13 @@
 // Nothing here allocates device memory; every kernel goes onto the caller's stream, except that
 // sparge_forward, beyond short calls, runs three passes on a second stream between a fork and a join on the caller's.  Only
 // sparge_tune synchronises (it decides on the host between candidates).
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <algorithm>
+#include <exception>
 #include <mutex>
 #include <vector>
 
@@ -611,6 +613,7 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
     if (n_inputs < 1 || !Q || !K || !V) return fail(SPARGE_EINVAL, "no inputs");
     if (n_tau < 1 || n_theta < 1 || n_lambda < 0 || !tau_grid || !theta_grid || (n_lambda && !lambda_grid))
         return fail(SPARGE_EINVAL, "empty tau/theta grid or missing lambda grid");
+    if ((long long)n_tau * n_theta > INT_MAX) return fail(SPARGE_EINVAL, "n_tau * n_theta too large");
     if (!tau || !theta || !lambda) return fail(SPARGE_EINVAL, "result arrays are NULL");
     for (int n = 0; n < n_inputs; ++n) {
         if (!Q[n] || !K[n] || !V[n]) return fail(SPARGE_EINVAL, "input %d has a NULL tensor", n);
@@ -635,6 +638,23 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
     void* o_cur = at<char>(ws, t.o_cur);
     hipError_t e;
     AttnStart start;
+    // Settings are enqueued one after the other and read back together: each writes its error sums {2 doubles} and
+    // counters {4 uint64} per (batch, head) into a slot of its input, and the host waits once per batch of slots.  The
+    // slots lie where the K mean was (d floats per (batch, head)), which nothing reads after the quantization.
+    const size_t slot_bytes = (size_t)BH * (2 * sizeof(double) + 4 * sizeof(uint64_t));
+    const int batch = static_cast<int>((size_t)BH * s.d * sizeof(float) / slot_bytes);   // 5 (d = 64) or 10 (d = 128)
+    const int n1 = n_tau * n_theta;
+    std::vector<char> host;                              // the slots of a batch, as read back
+    std::vector<double> t1, t2, best_sp, best_err;       // the tables of both stages, the chosen settings
+    try {
+        host.resize(slot_bytes * std::min(batch, std::max(n1, n_lambda)) * n_inputs);
+        t1.resize((size_t)n1 * H * 2);
+        t2.resize((size_t)n_lambda * H * 2);
+        best_sp.resize(H);
+        best_err.resize(H);
+    } catch (const std::exception&) {
+        return fail(SPARGE_ENOSPACE, "no host memory for the search's tables (%d + %d settings)", n1, n_lambda);
+    }
 
     // per input, once: block statistics, quantization, V tiles, and the full attention it is measured against
     HeadParams off;
@@ -657,11 +677,6 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
             hipSuccess) return hip_fail(e, "logits");
     }
 
-    // Settings are enqueued one after the other and read back together: each writes its error sums {2 doubles} and
-    // counters {4 uint64} per (batch, head) into a slot of its input, and the host waits once per batch of slots.  The
-    // slots lie where the K mean was (d floats per (batch, head)), which nothing reads after the quantization.
-    const size_t slot_bytes = (size_t)BH * (2 * sizeof(double) + 4 * sizeof(uint64_t));
-    const int batch = static_cast<int>((size_t)BH * s.d * sizeof(float) / slot_bytes);   // 5 (d = 64) or 10 (d = 128)
     auto slot = [&](int n, int k) { return at<char>(fwd(n), w.k_mean) + k * slot_bytes; };
     auto enqueue = [&](const HeadParams& tp, const HeadParams& thp, const HeadParams& lp, int k) -> int {
         for (int n = 0; n < n_inputs; ++n) {
@@ -680,7 +695,6 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
         return SPARGE_OK;
     };
     // the first k_n slots of every input -> per setting and head the mean sparsity and the worst relative L1
-    std::vector<char> host(slot_bytes * std::min(batch, std::max(n_tau * n_theta, n_lambda)) * n_inputs);
     auto collect = [&](int k_n, double* sp_err) -> int {
         const size_t bytes = slot_bytes * k_n;
         for (int n = 0; n < n_inputs; ++n)
@@ -713,8 +727,6 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
     };
 
     // stage 1: the (tau, theta) grid with the lambda test off
-    const int n1 = n_tau * n_theta;
-    std::vector<double> t1((size_t)n1 * H * 2);
     HeadParams tp, thp, lp;
     std::memset(&tp, 0, sizeof(tp));
     std::memset(&thp, 0, sizeof(thp));
@@ -729,7 +741,6 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
         }
         if ((rc = collect(k_n, &t1[(size_t)k0 * H * 2]))) return rc;
     }
-    std::vector<double> best_sp(H), best_err(H);
     for (int h = 0; h < H; ++h) {
         int best = -1;
         for (int k = 0; k < n1; ++k) {  // the sparsest admissible pair; the earlier one of equals
@@ -753,7 +764,6 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
 
     // stage 2: the lambda grid at each head's own (tau, theta)
     std::memset(&lp, 0, sizeof(lp));
-    std::vector<double> t2((size_t)n_lambda * H * 2);
     for (int c0 = 0; c0 < n_lambda; c0 += batch) {
         const int k_n = std::min(batch, n_lambda - c0);
         for (int k = 0; k < k_n; ++k) {

@@ -82,6 +82,32 @@ def test_workspaces_hold_what_their_entry_points_use(B, H, N, d):
         assert n.value == inputs * (of(sp.WS_FORWARD) + up(BH * N * d * 2)) + up(BH * N * d * 2)
 
 
+def test_search_without_host_memory_is_an_error_code():
+    """The search's host tables are allocated before anything is enqueued; where they do not fit, the call returns
+    SPARGE_ENOSPACE: no exception leaves the C entry.  (In a process of its own with its address space bounded, and
+    without a GPU: the device pointers are made up.)"""
+    import subprocess
+    import sys
+    code = """
+import ctypes, resource
+import paper_2502_18137_amd as sp
+from paper_2502_18137_amd.binding import _Desc
+lib = sp.load_library()
+n = 1 << 20                                         # a table of 2 GiB at 128 heads
+one, lam = (ctypes.c_float * 1)(0.5), (ctypes.c_float * n)(*[-1.0] * n)
+res, ptr = (ctypes.c_float * 128)(), (ctypes.c_void_p * 1)(4096)
+desc = _Desc(1, 128, 64, 64, 1, 128 * 64 * 64, 64 * 64, 64)
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (1 << 30),) * 2)
+rc = lib.sparge_tune(ptr, ptr, ptr, 1, ctypes.byref(desc), one, 1, one, 1, lam, n, 0.1, 0.1, 0.0, 0, res, res, res, None, None, None,
+                     None, ctypes.c_void_p(4096), 1 << 40, None)
+assert rc == -3 and b"host memory" in lib.sparge_last_error(), (rc, lib.sparge_last_error())
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="", PYTHONPATH=ROOT)
+    r = subprocess.run([sys.executable, "-c", code], env=env, cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
 def test_missing_library_fails_loudly(monkeypatch):
     import paper_2502_18137_amd.binding as b
     monkeypatch.setattr(b, "_LIB", None)
