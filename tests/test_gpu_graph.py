@@ -1,7 +1,9 @@
-"""The library allocates nothing, never synchronises (sparge_tune aside) and clears its counters with a fill
-kernel, so a caller may record its calls into a HIP graph.  Recorded here: the whole of Algorithm 1
+"""The library allocates nothing, never synchronises (sparge_tune aside) and sets its counters inside its kernels,
+so a caller may record its calls into a HIP graph.  Recorded here: the whole of Algorithm 1
 (sparge_forward) in its three product variants; every replay, with other eager work and synchronisations
-in between, must reproduce the eager result bit for bit, also after the inputs change in place."""
+in between, must reproduce the eager result bit for bit, also after the inputs change in place.  Two sizes: a short call
+(three launches on one stream, no more items than resident workgroups, so no item counters), and one beyond short calls
+(the fork onto the library's second stream and the join are captured, and the items are drawn from counters)."""
 import numpy as np
 import pytest
 
@@ -19,12 +21,22 @@ def sp():
     return sp
 
 
-@pytest.mark.parametrize("variant", [{}, {"pv_fp8": True}, {"qk16": True}], ids=["int8_16bit", "fp8_pv", "qk16"])
-def test_forward_replays_from_a_graph(sp, variant):
+def assert_forks_and_counts(N, H):
+    """sparge_forward forks onto the second stream beyond 256 key blocks, and an attention launch draws items from
+    counters when they are more than the resident workgroups (two per compute unit)."""
     import torch
-    w = small_workload("graph", N=1500, d=128, dtype="bf16", H=3, seed=12)
+    assert (N + 63) // 64 > 256 and H * ((N + 127) // 128) > 2 * torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("N,H", [(1500, 3), (16500, 4)], ids=["short", "forked"])
+@pytest.mark.parametrize("variant", [{}, {"pv_fp8": True}, {"qk16": True}], ids=["int8_16bit", "fp8_pv", "qk16"])
+def test_forward_replays_from_a_graph(sp, variant, N, H):
+    import torch
+    if N > 1500:
+        assert_forks_and_counts(N, H)
+    w = small_workload("graph", N=N, d=128, dtype="bf16", H=H, seed=12)
     x, Q, K, V = gpu_inputs(w)
-    w2 = small_workload("graph2", N=1500, d=128, dtype="bf16", H=3, seed=13)
+    w2 = small_workload("graph2", N=N, d=128, dtype="bf16", H=H, seed=13)
     x2, Q2, K2, V2 = gpu_inputs(w2)
     ws = torch.empty(sp.sparge_workspace_bytes(Q, sp.WS_FORWARD, variant.get("pv_fp8", False)), dtype=torch.uint8,
                      device="cuda")
@@ -55,15 +67,18 @@ def test_forward_replays_from_a_graph(sp, variant):
         assert torch.isfinite(junk)
 
 
-def test_two_graphs_replayed_on_two_streams(sp):
+@pytest.mark.parametrize("N,H", [(4000, 6), (16500, 4)], ids=["short", "forked"])
+def test_two_graphs_replayed_on_two_streams(sp, N, H):
     """Two captures of sparge_forward, each with its own workspace, outputs and inputs (one causal), replayed at
     the same time on two streams, three rounds with eager launches in between: every replay reproduces its
-    eager result bit for bit.  (The item counters of the attention kernel live in each call's workspace: two
-    launches in flight share nothing.)"""
+    eager result bit for bit.  (The item counters of the attention kernel, which the larger size draws from, live in
+    each call's workspace: two launches in flight share nothing.)"""
     import torch
+    if N > 4000:
+        assert_forks_and_counts(N, H)
     cases = []
     for seed, causal, d in ((21, False, 128), (22, True, 64)):
-        w = small_workload(f"g{seed}", N=4000, d=d, dtype="bf16", H=6, seed=seed, causal=causal)
+        w = small_workload(f"g{seed}", N=N, d=d, dtype="bf16", H=H, seed=seed, causal=causal)
         x, Q, K, V = gpu_inputs(w)
         eager, mask, stats = sp.sparge_forward(Q, K, V, w.tau, w.theta, w.lam, causal=causal, return_mask=True,
                                                return_stats=True)

@@ -114,3 +114,26 @@ def test_rel_l1_and_tuner_are_reproducible(sp):
     for r in runs[1:]:
         assert np.array_equal(r["stage1"], runs[0]["stage1"]) and np.array_equal(r["stage2"], runs[0]["stage2"])
         assert r["tau"] == runs[0]["tau"] and r["theta"] == runs[0]["theta"] and r["lam"] == runs[0]["lam"]
+
+
+@pytest.mark.parametrize("d,pv_fp8", [(64, False), (128, False), (128, True)])
+def test_grids_of_several_batches_equal_searches_of_single_settings(sp, d, pv_fp8):
+    """The search reads its settings back in batches (5 at d = 64, 10 at d = 128).  Grids of 12 pairs and 11 lambdas, which
+    cross a batch in both stages at either size, on two inputs and two batch entries: every row of both tables has the
+    bits of a search of that one setting."""
+    import torch
+    ws = [small_workload(f"batch{i}", N=700, d=d, dtype="bf16", H=4, seed=70 + i, noise=0.5) for i in range(2)]
+    inputs = [tuple(to_torch(make_workload(w)[t].reshape(2, 2, 700, d), "bf16") for t in "qkv") for w in ws]
+    taus, thetas = [0.5, 0.7, 0.9, 0.95], [-0.5, 0.4, 0.8]
+    lams = [-12.0, -10.0, -8.0, -6.0, -5.0, -4.0, -3.5, -3.0, -2.5, -2.0, -1.5]
+    print(f"d={d} pv_fp8={pv_fp8}", flush=True)
+    got = sp.sparge_tune(inputs, taus, thetas, lams, 0.06, 0.08, pv_fp8=pv_fp8)
+    for a, tau in enumerate(taus):
+        for b, theta in enumerate(thetas):
+            one = sp.sparge_tune(inputs, [tau], [theta], lams[:1], 0.06, 0.08, pv_fp8=pv_fp8)
+            assert np.array_equal(got["stage1"][a, b], one["stage1"][0, 0]), (tau, theta)
+    assert len(np.unique(got["stage1"][..., 0, 0])) > 6                # the settings do differ
+    for h in range(2):                                                 # stage 2 of a head runs at its own pair
+        for c, lam in enumerate(lams):
+            one = sp.sparge_tune(inputs, [got["tau"][h]], [got["theta"][h]], [lam], 0.06, 0.08, pv_fp8=pv_fp8)
+            assert np.array_equal(got["stage2"][c, h], one["stage2"][0, h]), (h, lam)
