@@ -145,8 +145,8 @@ int sparge_predict_static(const void* Q, const void* K, const sparge_desc* desc,
  * P~V row-group products executed, tiles a full attention needs, row-group products a full
  * attention needs}; it is overwritten, not accumulated.
  * Work distribution: the launch is two resident workgroups per compute unit that take (head, Q block)
- * items from eight counters (one per XCD range of items) kept in `ws` and set by an earlier kernel of the call
- * in front of the launch; which workgroup computes an item depends on timing, the result does not.
+ * items: the first by position, further ones from eight counters (one per XCD range of items) kept in `ws` and set
+ * by an earlier kernel of the call; which workgroup computes an item depends on timing, the result does not.
  */
 int sparge_attn_quantized(const int8_t* Qq, const int8_t* Kq, const float* q_scale, const float* k_scale,
                           const void* V, const sparge_desc* desc, const uint8_t* mask,
@@ -208,7 +208,8 @@ int sparge_attn(const void* Q, const void* K, const void* V, const sparge_desc* 
  * All of Algorithm 1: Quant, predict M_g, masked loop with the lambda skip.  Q and K are each read
  * once for block statistics + Q quantization and K is read a second time for its quantization.
  * mask_out: optional uint8 [B,H,T_m,T_n] receiving M_g (NULL: kept in `ws` only).
- * Streams: short calls (at most 256 key blocks and about 2^24 elements per tensor) run on `hip_stream` alone.
+ * Streams: short calls (at most 128 key blocks and 3 * 2^23 elements per tensor, or 256 key blocks and 2^24
+ * elements) run on `hip_stream` alone.
  * Otherwise the V tiles, the K mean and the K quantization run on a second stream that the library
  * keeps per device (created at the first call on that device, default priority, never destroyed),
  * forked from `hip_stream` after the block statistics and joined to it before the attention kernel,
@@ -249,8 +250,9 @@ int sparge_rel_l1(const void* O, const void* O_ref, const sparge_desc* desc, dou
  * tau, theta, lambda [H] (lambda = -INFINITY: stage 2 stays off); optional sparsity, l1_out [H] of the
  * chosen setting; optional tables stage1 [n_tau,n_theta,H,2] and stage2 [n_lambda,H,2] = {mean
  * sparsity, worst error}.  pv_dtype of desc selects the P~V product that is tuned.
- * This is the one entry point that synchronises: it reads counters back after every candidate, and it
- * blocks until the stream has finished.  Workspace: sparge_tune_workspace_bytes (256-byte aligned).
+ * This is the one entry point that synchronises: it reads error sums and counters back after every 5 (d = 64) or
+ * 10 (d = 128) candidates, and it blocks until the stream has finished.  Workspace: sparge_tune_workspace_bytes
+ * (256-byte aligned).  SPARGE_ENOSPACE also where the host has no memory for the tables.
  */
 int sparge_tune_workspace_bytes(const sparge_desc* desc, int n_inputs, size_t* bytes /* host, out */);
 int sparge_tune(const void* const* Q, const void* const* K, const void* const* V, int n_inputs,

@@ -1,7 +1,7 @@
 // C ABI of libsparge: argument validation, workspace partition, kernel sequencing.
 // Nothing here allocates device memory; every kernel goes onto the caller's stream, except that
 // sparge_forward, beyond short calls, runs three passes on a second stream between a fork and a join on the caller's.  Only
-// sparge_tune synchronises (it decides on the host between candidates).
+// sparge_tune synchronises (it reads batches of candidates back and decides on the host).
 #include <climits>
 #include <cmath>
 #include <cstdarg>
@@ -516,7 +516,7 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
     if (short_call(s)) {
         lock.unlock();
         // Three launches on the caller's stream: block statistics with the V tiles; predictor beside the K
-        // quantization; attention.  (The FP8 tiles need V's maxima first: launches of their own.)
+        // quantization; attention.  (The FP8 tiles need V's maxima first: three launches more, ahead of them.)
         if (s.pv_fp8 && (e = retile_v(V, s, at<char>(ws, w.v_tiles), st)) != hipSuccess) return hip_fail(e, "v_tiles");
         if ((e = launch_prep(Q, K, V, s, at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t), at<double>(ws, w.sim_q),
                              at<double>(ws, w.sim_k), Qq, q_scale, s.pv_fp8 ? nullptr : at<uint16_t>(ws, w.v_tiles), start,

@@ -144,10 +144,12 @@ hipError_t launch_block_stats(const void* Q, const void* K, const Shape& s, doub
 // Short calls take the block statistics (and V tiles) in one launch and the predictor with the K quantization in
 // another.  Up to 256 key blocks (a row's logits fit the LDS of a workgroup of 8 rows at full occupancy) and as many
 // elements per tensor as below: a launch, an event and a wait saved are then worth more than what the passes lose in one
-// kernel (the registers of the hungriest, the mean summed once per workgroup).  Whole forward passes, several launches
-// on two streams against these: 67 / 32 us at 2 x 2048 x 64, 191 / 170 at 24 x 4173 x 128, 378 / 348 at 8 x 16384 x 64,
-// 199 / 183 at 48 x 3000 x 128, 172 / 166 at 192 x 1024 x 128; beyond the line 750 / 776 at 12 x 16000 x 128,
-// 595 / 603 at 32 x 8192 x 128, 218 / 218 at 256 x 1024 x 128.
+// kernel (the registers of the hungriest, the mean summed once per workgroup).  Separate launches against these, us, whole
+// forward pass and predictor alone: 81 / 22, 24 / 18 at 4 x 64 x 64; 172 / 166, 37.4 / 31.4 at 192 x 1024 x 128;
+// 324 / 317, 35.1 / 32.6 at 16 x 8192 x 128; 468 / 471, 41.6 / 40.2 at 24 x 8192 x 128 (on the line); 373 / 356,
+// 27.4 / 24.9 at 8, 531 / 519, 32.6 / 28.7 at 12 and 694 / 677, 36.0 / 32.5 at 16 x 16384 x 64 (on the line);
+// 564 / 558, 37.2 / 37.3 at 8 x 16384 x 128 (on the line).  Beyond it the two part: 851 / 841, 40.8 / 42.9 at
+// 20 x 16384 x 64, 819 / 830, 44.4 / 44.2 at 12 x 16384 x 128, 490 / 487, 40.2 / 37.6 at 12 x 12000 x 128.
 inline bool short_call(const Shape& s) {
     return s.Tn <= 256 && (long long)s.B * s.H * s.N * s.d <= (s.Tn <= 128 ? 3ll << 23 : 1ll << 24);
 }

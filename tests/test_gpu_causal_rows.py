@@ -1,6 +1,7 @@
-"""Causal rows rank only the key blocks they see, with a quarter, half or all of the ranks a full row takes, and logits that no
-row sees are not computed.  Sequence lengths whose rows cross every one of these edges (ranks per lane 4 and less, 8, 16,
-32, and the rows sorted in LDS), ragged ends, workspaces filled with NaN: the mask against the oracle."""
+"""Causal rows of up to 2048 key blocks rank only the key blocks they see, with a quarter, half or all of the ranks a full row
+takes; longer rows are sorted in LDS with all their ranks, the unseen ones masked.  Logits that no row sees are not computed in
+either.  Sequence lengths whose rows cross every one of these edges (ranks per lane 4 and less, 8, 16, 32, and the rows
+sorted in LDS), ragged ends, workspaces filled with NaN: the mask against the oracle."""
 import pytest
 
 from oracle import sparge_oracle as so
