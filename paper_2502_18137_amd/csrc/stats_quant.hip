@@ -285,11 +285,23 @@ __global__ __launch_bounds__(256) void v_tiles_kernel(const uint16_t* __restrict
     v_tile<D>(tile, V + b * s.sb + h * s.sh, s, (long long)b * s.H + h, j, tiles);
 }
 
-// 16 K blocks side by side fill the 128-byte lines of the channel sums ([d][Tn] doubles, one from each block): the
-// workgroups of such 16 blocks run on one XCD (numbers equal modulo 8), whose L2 then writes whole lines.  Measured on
-// the predictor call: 105.1 against 108.1 us at 24 heads x 22272 x 128, 77.1 against 80.8 us at 512 heads x 1024 x 128.
-__device__ __forceinline__ int k_block_of(int id, int n) {
-    return id < n / 128 * 128 ? id / 128 * 128 + (id % 8) * 16 + id % 128 / 8 : id;
+// Which K block the workgroup (bh, t) of the launch takes.  The channel sums are [bh][d][Tn] doubles, one from each block, so
+// 16 blocks side by side fill a 128-byte line, and it should be one XCD (workgroup numbers equal modulo 8) whose L2 does.
+// Each XCD takes an eighth of a head's blocks; heads of fewer than 16 blocks share lines among channels instead, and
+// 128 consecutive blocks are dealt out 16 to an XCD across heads.  Measured against no reordering, us: predictor 456 / 478 at
+// 32 x 65536 x 128, 105 / 110 at 24 x 22272 x 128, 73.0 / 76.7 at 512 x 1024 x 128 (16 blocks), sparge_quantize 120 / 125 at
+// 2048 x 200 x 128 (4 blocks).  Dealing out across heads everywhere costs three divisions per workgroup, 470 and 106 us.
+constexpr int K_BLOCKS_OF_ITS_OWN = 16;
+__device__ __forceinline__ void k_block_of(const Shape& s, int& bh, int& t) {
+    if (s.Tn >= K_BLOCKS_OF_ITS_OWN) {
+        if (t < (s.Tn & ~7)) t = (t & 7) * (s.Tn >> 3) + (t >> 3);
+    } else {
+        const int id = bh * s.Tn + t;
+        if (id < ((s.B * s.H * s.Tn) & ~127)) {
+            const int to = (id & ~127) + (id & 7) * 16 + ((id & 127) >> 3);
+            bh = to / s.Tn, t = to % s.Tn;
+        }
+    }
 }
 
 template <int D, int DT, int ROWS, bool KSIDE, bool QUANT, bool STATS>
@@ -299,10 +311,12 @@ __global__ __launch_bounds__(256) void block_stats_kernel(const uint16_t* __rest
                                                           AttnStart start) {
     __shared__ StatsLds<D> lds;
     int t = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    if (t + h + b == 0) set_start(start, 0, 1);
     if constexpr (KSIDE) {
-        const int id = k_block_of((b * s.H + h) * s.Tn + t, s.B * s.H * s.Tn);
-        t = id % s.Tn, h = id / s.Tn % s.H, b = id / s.Tn / s.H;
+        int bh = b * s.H + h;
+        k_block_of(s, bh, t);
+        if (s.Tn < K_BLOCKS_OF_ITS_OWN) b = bh / s.H, h = bh % s.H;
+    } else if (t + h + b == 0) {
+        set_start(start, 0, 1);
     }
     block_stats<D, DT, ROWS, KSIDE, QUANT, STATS>(lds, X + b * s.sb + h * s.sh, s, (long long)b * s.H + h, t, pooled, sim,
                                                   Xq, scale);
@@ -333,9 +347,9 @@ __global__ __launch_bounds__(256) void prep_kernel(const uint16_t* __restrict__ 
     }
     id -= nq;
     if (id < nk) {
-        id = k_block_of(id, nk);
-        const int bh = id / s.Tn;
-        block_stats<D, DT, BK, true, false, true>(lds.stats, at(K, bh), s, bh, id % s.Tn, ksum_t, sim_k, nullptr, nullptr);
+        int bh = id / s.Tn, t = id % s.Tn;
+        k_block_of(s, bh, t);
+        block_stats<D, DT, BK, true, false, true>(lds.stats, at(K, bh), s, bh, t, ksum_t, sim_k, nullptr, nullptr);
         return;
     }
     id -= nk;
