@@ -247,13 +247,13 @@ int run_predict(const Shape& s, void* ws, const Workspace& w, const HeadParams& 
     return SPARGE_OK;
 }
 
-int plan_attn(const Shape& s, void* queue, uint64_t* stats, AttnStart* start) {
-    const hipError_t e = plan_start(s, static_cast<unsigned int*>(queue), reinterpret_cast<unsigned long long*>(stats), start);
+int plan_attn(const Shape& s, int causal, void* queue, uint64_t* stats, AttnStart* start) {
+    const hipError_t e = plan_start(s, causal, static_cast<unsigned int*>(queue), reinterpret_cast<unsigned long long*>(stats), start);
     return e == hipSuccess ? SPARGE_OK : hip_fail(e, "plan of the attention launch");
 }
 // The same for an attention launch whose call has no earlier kernel that could set its counters.
-int plan_and_set_attn(const Shape& s, void* queue, uint64_t* stats, AttnStart* start, hipStream_t st) {
-    const int rc = plan_attn(s, queue, stats, start);
+int plan_and_set_attn(const Shape& s, int causal, void* queue, uint64_t* stats, AttnStart* start, hipStream_t st) {
+    const int rc = plan_attn(s, causal, queue, stats, start);
     if (rc) return rc;
     const hipError_t e = launch_set_start(*start, st);
     return e == hipSuccess ? SPARGE_OK : hip_fail(e, "set the attention launch's counters");
@@ -412,7 +412,7 @@ int sparge_attn_quantized(const int8_t* Qq, const int8_t* Kq, const float* q_sca
     if ((rc = check_ws(w, ws, ws_bytes))) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     AttnStart start;
-    if ((rc = plan_and_set_attn(s, at<void>(ws, w.queue), stats, &start, st))) return rc;
+    if ((rc = plan_and_set_attn(s, causal, at<void>(ws, w.queue), stats, &start, st))) return rc;
     return run_attn(Qq, Kq, q_scale, k_scale, V, s, at<char>(ws, w.v_tiles), mask, lam, sm_scale, causal, O,
                     stats, start, st);
 }
@@ -453,7 +453,7 @@ int sparge_attn_tiled(const int8_t* Qq, const int8_t* Kq, const float* q_scale, 
     if ((rc = check_ws(w, ws, ws_bytes))) return rc;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     AttnStart start;
-    if ((rc = plan_and_set_attn(s, at<void>(ws, w.queue), stats, &start, st))) return rc;
+    if ((rc = plan_and_set_attn(s, causal, at<void>(ws, w.queue), stats, &start, st))) return rc;
     return timed_attn(Qq, Kq, q_scale, k_scale, v_tiles, s, mask, lam, sm_scale, causal, O, stats, start, st);
 }
 
@@ -473,11 +473,11 @@ int sparge_attn(const void* Q, const void* K, const void* V, const sparge_desc* 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     AttnStart start;
     if (s.qk16) {  // the products run on Q and K as they are: nothing to quantize
-        if ((rc = plan_and_set_attn(s, at<void>(ws, w.queue), stats, &start, st))) return rc;
+        if ((rc = plan_and_set_attn(s, causal, at<void>(ws, w.queue), stats, &start, st))) return rc;
         return run_attn(Q, K, nullptr, nullptr, V, s, at<char>(ws, w.v_tiles), mask, lam, sm_scale, causal, O, stats,
                         start, st);
     }
-    if ((rc = plan_attn(s, at<void>(ws, w.queue), stats, &start))) return rc;
+    if ((rc = plan_attn(s, causal, at<void>(ws, w.queue), stats, &start))) return rc;
     if ((rc = run_stats_and_quant(Q, K, s, nullptr, at<double>(ws, w.ksum_t), nullptr, nullptr, at<int8_t>(ws, w.Qq),
                                   at<float>(ws, w.q_scale), at<int8_t>(ws, w.Kq), at<float>(ws, w.k_scale),
                                   at<float>(ws, w.k_mean), start, st))) return rc;
@@ -510,7 +510,7 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
     float* q_scale = q8 ? at<float>(ws, w.q_scale) : nullptr;
     AttnStart start;
     hipError_t e;
-    if ((rc = plan_attn(s, at<void>(ws, w.queue), stats, &start))) return rc;
+    if ((rc = plan_attn(s, causal, at<void>(ws, w.queue), stats, &start))) return rc;
     std::unique_lock<std::mutex> lock(g_side_mutex);
     SideStream* side = side_stream();   // short calls do not use it, but a first call of any length makes it
     if (short_call(s)) {
@@ -666,7 +666,7 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
                                       at<double>(f, w.sim_q), at<double>(f, w.sim_k), at<int8_t>(f, w.Qq),
                                       at<float>(f, w.q_scale), at<int8_t>(f, w.Kq), at<float>(f, w.k_scale),
                                       at<float>(f, w.k_mean), AttnStart{}, st))) return rc;
-        if ((rc = plan_and_set_attn(s, at<void>(f, w.queue), nullptr, &start, st))) return rc;
+        if ((rc = plan_and_set_attn(s, causal, at<void>(f, w.queue), nullptr, &start, st))) return rc;
         if ((rc = run_attn(at<int8_t>(f, w.Qq), at<int8_t>(f, w.Kq), at<float>(f, w.q_scale), at<float>(f, w.k_scale),
                            V[n], s, at<char>(f, w.v_tiles), nullptr, off, sm_scale, causal, o_ref(n), nullptr,
                            start, st)))
@@ -686,7 +686,7 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
             int r;
             if ((e = launch_topcdf(at<double>(f, w.logits), at<double>(f, w.sim_q), at<double>(f, w.sim_k), s, tp, thp, causal,
                                    at<uint8_t>(f, w.mask), st)) != hipSuccess) return hip_fail(e, "topcdf");
-            if ((r = plan_and_set_attn(s, at<void>(f, w.queue), counters, &start, st))) return r;
+            if ((r = plan_and_set_attn(s, causal, at<void>(f, w.queue), counters, &start, st))) return r;
             if ((r = timed_attn(at<int8_t>(f, w.Qq), at<int8_t>(f, w.Kq), at<float>(f, w.q_scale),
                                 at<float>(f, w.k_scale), at<char>(f, w.v_tiles), s, at<uint8_t>(f, w.mask), lp,
                                 sm_scale, causal, o_cur, counters, start, st))) return r;

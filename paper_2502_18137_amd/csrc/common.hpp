@@ -179,13 +179,28 @@ hipError_t launch_v_tiles(const void* V, const Shape& s, uint16_t* v_tiles, hipS
 hipError_t launch_mask_lut(const uint8_t* mask, const Shape& s, int32_t* lut, int32_t* lut_count, hipStream_t st);
 // What an attention launch of this shape needs set, with its counters in ATTN_QUEUE_BYTES of device memory at `memory`
 // that no other launch may use at the same time; launch_set_start sets it where no other kernel does.
-hipError_t plan_start(const Shape& s, unsigned int* memory, unsigned long long* stats, AttnStart* start);
+hipError_t plan_start(const Shape& s, int causal, unsigned int* memory, unsigned long long* stats, AttnStart* start);
 hipError_t launch_set_start(const AttnStart& start, hipStream_t st);
 // The sparse flash loop (accumulates into stats).
 hipError_t launch_attn(const void* Qp, const void* Kp, const float* q_scale, const float* k_scale,
                        const void* v_tiles, const float* v_scale, const Shape& s, const uint8_t* mask,
                        const HeadParams& lambda, float sm_scale, int causal, void* O, unsigned long long* stats,
                        const AttnStart& start, hipStream_t st);
+// Calls of few Q blocks: the same loop with a 32-row group per workgroup (attn_split.hip), the same bits.
+// attn_split_pays: a compute unit holds one workgroup of it, which runs a group's tiles in a half to two thirds of the
+// time attn.hip needs; so it is worth it while every group has a unit (us, attn.hip / this, the attention alone):
+//   16 x 70 x 64 7.4 / 4.8, 8 x 1024 x 64 16.9 / 9.4, 2 x 4096 x 64 36.9 / 21.0, 1 x 8192 x 64 50.4 / 28.5; with d = 128
+//   8.6 / 5.9, 20.2 / 11.9, 43.6 / 28.1, 58.5 / 37.1; beyond it, 12 x 1024 x 128 20.7 / 21.4, 4 x 4096 x 128 46.6 / 51.9.
+// Causal groups start with the longest, and the second ones a unit gets are the short ones: up to two per unit, while
+// rows are short (16 x 1024 16.8 / 12.8 at d = 64, 19.9 / 16.2 at 128; 4 x 4096 36.2 / 29.8, 43.9 / 40.4; beyond it
+// 2 x 5000 x 128 45.2 / 46.8; 20 x 1024 17.3 / 18.8, 20.1 / 24.8; not with the 16-bit Q K^T at d = 128, whose K tiles fill
+// the LDS: 4 x 4096 54.7 / 58.3, one per unit 2 x 4096 53.6 / 39.4).
+constexpr int SPLIT_MAX_TN = 256;    // key blocks its lists hold
+bool attn_split_pays(const Shape& s, int causal);
+hipError_t launch_attn_split(const void* Qp, const void* Kp, const float* q_scale, const float* k_scale,
+                             const void* v_tiles, const float* v_scale, const Shape& s, const uint8_t* mask,
+                             const HeadParams& lambda, float scale, int causal, void* O, unsigned long long* stats,
+                             hipStream_t st);
 // FP8 form of V: per-(b,h,channel) |V| maxima (as fp32 bit patterns, zeroed here), scales amax/448, and
 // E4M3 tiles in the operand order of the 32x32x64 MFMA.
 hipError_t launch_v_tiles_fp8(const void* V, const Shape& s, unsigned char* tiles, float* v_scale,

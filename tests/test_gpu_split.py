@@ -1,0 +1,44 @@
+"""Calls of few row groups run the flash loop with a workgroup per 32-row group whose waves share the group's tiles
+(attn_split.hip); larger calls give a row group to one wave (attn.hip).  Both decide, round and add in the same order, so a
+head in a call of its own must come out as the same head of a call that is too large for the shared form, bit for bit:
+output and execution counters.  Sizes at the edges of a row group, a key block, a round of four tiles and the longest
+list (256 key blocks); random masks with rows that keep nothing, scores wide enough for the reference maximum to move and for
+the stage-2 test to skip."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [1, 31, 33, 64, 65, 129, 256, 257, 700, 1100, 4173, 16321, 16384]
+
+
+@pytest.mark.parametrize("kw", [{}, {"pv_fp8": True}, {"qk16": True}], ids=["int8", "fp8", "qk16"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,dtype", [(64, "bf16"), (64, "fp16"), (128, "bf16"), (128, "fp16")])
+def test_a_head_of_its_own_equals_the_head_of_a_large_call(d, dtype, causal, kw):
+    import torch
+    import paper_2502_18137_amd as sp
+    dt = torch.float16 if dtype == "fp16" else torch.bfloat16
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    skipped = 0
+    for N in SIZES:
+        groups, Tm, Tn = (N + 31) // 32, (N + 127) // 128, (N + 63) // 64
+        heads = 2 * units // groups + 1                     # one more than the shared form takes, causal or not
+        H = min(heads, 128)
+        B = -(-heads // H)
+        keep, lam = (1.0, -3.0) if N % 2 else (0.4, -1.5)
+        print(f"B={B} H={H} N={N} d={d} {dtype} causal={causal} {kw}", flush=True)
+        g = torch.Generator(device="cuda").manual_seed(N + d)
+        wide = 1 + 1.5 * torch.randn(B, H, Tn, 1, generator=g, device="cuda").abs().repeat_interleave(64, 2)[:, :, :N]
+        Q, K, V = ((torch.randn(B, H, N, d, generator=g, device="cuda") * wide).to(dt) for _ in range(3))
+        mask = (torch.rand(B, H, Tm, Tn, generator=g, device="cuda") < keep).to(torch.uint8)
+        mask[0, 0, Tm // 2] = 0                             # a Q block that keeps nothing
+        args = dict(causal=causal, return_stats=True, **kw)
+        O, stats = sp.sparge_attn(Q, K, V, mask, lam, **args)
+        assert torch.isfinite(O.float()).all()
+        skipped += int((stats[..., 3] - stats[..., 1]).sum())
+        for b, h in {(0, 0), (B - 1, H - 1)}:
+            one = tuple(t[b:b + 1, h:h + 1] for t in (Q, K, V, mask.contiguous()))
+            o, st = sp.sparge_attn(*one[:3], one[3].contiguous(), lam, **args)
+            assert torch.equal(o, O[b:b + 1, h:h + 1]), (N, b, h)
+            assert torch.equal(st, stats[b:b + 1, h:h + 1]), (N, b, h)
+    assert skipped > 0
