@@ -251,8 +251,9 @@ int sparge_rel_l1(const void* O, const void* O_ref, const sparge_desc* desc, dou
  * chosen setting; optional tables stage1 [n_tau,n_theta,H,2] and stage2 [n_lambda,H,2] = {mean
  * sparsity, worst error}.  pv_dtype of desc selects the P~V product that is tuned.
  * This is the one entry point that synchronises: it reads error sums and counters back after every 5 (d = 64) or
- * 10 (d = 128) candidates, and it blocks until the stream has finished.  Workspace: sparge_tune_workspace_bytes
- * (256-byte aligned).  SPARGE_ENOSPACE also where the host has no memory for the tables.
+ * 10 (d = 128) candidates, or after up to 16 that small searches run in one launch on all inputs, and it blocks until the
+ * stream has finished.  Workspace: sparge_tune_workspace_bytes (256-byte aligned); a small search that gets less runs its
+ * candidates one by one if that fits.  SPARGE_ENOSPACE also where the host has no memory for the tables.
  */
 int sparge_tune_workspace_bytes(const sparge_desc* desc, int n_inputs, size_t* bytes /* host, out */);
 int sparge_tune(const void* const* Q, const void* const* K, const void* const* V, int n_inputs,

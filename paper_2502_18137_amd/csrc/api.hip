@@ -63,6 +63,7 @@ int check_desc(const sparge_desc* d, Shape* s) {
     if (d->qk_dtype != SPARGE_QK_INT8 && d->qk_dtype != SPARGE_QK_16BIT)
         return fail(SPARGE_EUNSUPPORTED, "qk_dtype %d not supported", d->qk_dtype);
     s->qk16 = d->qk_dtype == SPARGE_QK_16BIT;
+    s->op_bh = d->B * d->H, s->dense_bh = s->by_setting = s->one_mask = 0;
     if (s->qk16 && s->pv_fp8) return fail(SPARGE_EUNSUPPORTED, "the 16-bit Q K^T product is not built with the FP8 P~V product");
     if (s->qk16 && Tn > 2048) return fail(SPARGE_EUNSUPPORTED, "the 16-bit Q K^T product takes at most 2048 key blocks (N <= 131072)");
     if (s->qk16 && (double)Tn * BK * d->stride_n * 2.0 >= 4294967296.0)
@@ -261,13 +262,13 @@ int plan_and_set_attn(const Shape& s, int causal, void* queue, uint64_t* stats, 
 
 // The attention launch, bracketed by the caller's timing events when some are installed.  start: set already.
 int timed_attn(const void* Qq, const void* Kq, const float* q_scale, const float* k_scale,
-               const void* v_tiles, const Shape& s, const uint8_t* mask, const HeadParams& lam, float sm_scale,
+               const void* v_tiles, const float* v_scale, const Shape& s, const uint8_t* mask, const HeadParams& lam, float sm_scale,
                int causal, void* O, uint64_t* stats, const AttnStart& start, hipStream_t st) {
     const bool timed = g_ev_start && g_ev_k < g_ev_n;
     hipError_t e;
     if (timed && (e = hipEventRecord(static_cast<hipEvent_t>(g_ev_start[g_ev_k]), st)) != hipSuccess)
         return hip_fail(e, "record start event");
-    if ((e = launch_attn(Qq, Kq, q_scale, k_scale, v_tiles, v_scale_of(v_tiles, s), s, mask, lam, sm_scale, causal, O,
+    if ((e = launch_attn(Qq, Kq, q_scale, k_scale, v_tiles, v_scale, s, mask, lam, sm_scale, causal, O,
                          reinterpret_cast<unsigned long long*>(stats), start, st)) != hipSuccess)
         return hip_fail(e, "attn");
     if (timed) {
@@ -283,7 +284,7 @@ int run_attn(const void* Qq, const void* Kq, const float* q_scale, const float* 
              int causal, void* O, uint64_t* stats, const AttnStart& start, hipStream_t st) {
     hipError_t e;
     if ((e = retile_v(V, s, v_tiles, st)) != hipSuccess) return hip_fail(e, "v_tiles");
-    return timed_attn(Qq, Kq, q_scale, k_scale, v_tiles, s, mask, lam, sm_scale, causal, O, stats, start, st);
+    return timed_attn(Qq, Kq, q_scale, k_scale, v_tiles, v_scale_of(v_tiles, s), s, mask, lam, sm_scale, causal, O, stats, start, st);
 }
 
 }  // namespace
@@ -454,7 +455,7 @@ int sparge_attn_tiled(const int8_t* Qq, const int8_t* Kq, const float* q_scale, 
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     AttnStart start;
     if ((rc = plan_and_set_attn(s, causal, at<void>(ws, w.queue), stats, &start, st))) return rc;
-    return timed_attn(Qq, Kq, q_scale, k_scale, v_tiles, s, mask, lam, sm_scale, causal, O, stats, start, st);
+    return timed_attn(Qq, Kq, q_scale, k_scale, v_tiles, v_scale_of(v_tiles, s), s, mask, lam, sm_scale, causal, O, stats, start, st);
 }
 
 int sparge_attn(const void* Q, const void* K, const void* V, const sparge_desc* desc, const uint8_t* mask,
@@ -526,7 +527,7 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
                                       at<double>(ws, w.sim_k), K, s, t, th, sm_scale, causal, mask,
                                       q8 ? at<int8_t>(ws, w.Kq) : nullptr, at<float>(ws, w.k_scale), st)) != hipSuccess)
             return hip_fail(e, "predict");
-        return timed_attn(Qa, Ka, qsc, ksc, at<char>(ws, w.v_tiles), s, mask, lam, sm_scale, causal, O, stats, start, st);
+        return timed_attn(Qa, Ka, qsc, ksc, at<char>(ws, w.v_tiles), v_scale_of(at<char>(ws, w.v_tiles), s), s, mask, lam, sm_scale, causal, O, stats, start, st);
     }
     if (!side) {
         if ((rc = run_stats_and_quant(Q, K, s, at<double>(ws, w.pooled_q), at<double>(ws, w.ksum_t),
@@ -559,7 +560,7 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
     if ((e = hipStreamWaitEvent(st, side->join, 0)) != hipSuccess) return hip_fail(e, "wait join");
     if (rc_side) return rc_side;
     if (rc) return rc;
-    return timed_attn(Qa, Ka, qsc, ksc, at<char>(ws, w.v_tiles), s, mask, lam, sm_scale, causal, O, stats, start, st);
+    return timed_attn(Qa, Ka, qsc, ksc, at<char>(ws, w.v_tiles), v_scale_of(at<char>(ws, w.v_tiles), s), s, mask, lam, sm_scale, causal, O, stats, start, st);
 }
 
 int sparge_rel_l1(const void* O, const void* O_ref, const sparge_desc* desc, double* out, void* hip_stream) {
@@ -574,19 +575,53 @@ int sparge_rel_l1(const void* O, const void* O_ref, const sparge_desc* desc, dou
 
 namespace {
 
-// Workspace of the hyper-parameter search: per input a forward workspace and the full-attention output,
-// then one output buffer.  (The error sums and counters lie inside the forward workspaces.)
+// Workspace of the hyper-parameter search.  The operands of the inputs lie one behind the other, as further batch entries,
+// so that one launch can run several settings on several inputs (Shape: op_bh); outputs are kept packed [B,H,N,d].
 struct TuneWs {
-    size_t fwd_bytes, out_bytes, per_input, o_cur, total;
+    int group, settings;   // inputs and settings of one launch
+    int batch;             // settings between two waits of the host
+    size_t pooled_q, ksum_t, sim_q, sim_k, k_mean, logits, Qq, Kq, q_scale, k_scale, v_tiles, o_ref, o_cur, mask, slots, queue, total;
 };
-TuneWs tune_layout(const Shape& s, int n_inputs) {
+// Error sums {2 doubles} and counters {4 uint64} of one setting on one input.
+size_t tune_slot_bytes(const Shape& s) { return (size_t)s.B * s.H * (2 * sizeof(double) + 4 * sizeof(uint64_t)); }
+// A launch takes all inputs, and settings enough for two items a resident workgroup, where a setting on all inputs has
+// no more items than workgroups are resident: 593 -> 184 us (4 x 1536 x 64, two inputs, six settings: 14 attention launches
+// and 24 others one after the other before), 932 -> 516 at 16 x 2048 x 128 (on the line).  Else a setting on an input, and the settings of a batch leave their sums where the K mean was (d floats per
+// (batch, head)), which nothing reads after the quantization.
+TuneWs tune_layout(const Shape& s, int n_inputs, bool one_by_one) {
+    constexpr long long FEW_ITEMS = 512, LAUNCH_ITEMS = 1024;
+    constexpr int MAX_SETTINGS = 16;
+    const size_t n = n_inputs, BH = (size_t)s.B * s.H;
+    const long long items = (long long)n_inputs * s.B * s.H * s.Tm;
     TuneWs t{};
-    t.fwd_bytes = align256(plan(s, SPARGE_WS_FORWARD).total);
-    const size_t span = (size_t)(s.B - 1) * s.sb + (size_t)(s.H - 1) * s.sh + (size_t)(s.N - 1) * s.sn + s.d;
-    t.out_bytes = align256(span * sizeof(uint16_t));
-    t.per_input = t.fwd_bytes + t.out_bytes;
-    t.o_cur = t.per_input * n_inputs;
-    t.total = t.o_cur + t.out_bytes;
+    const bool many = !one_by_one && items <= FEW_ITEMS && (long long)n_inputs * s.B * s.H * (MAX_SETTINGS + 1) <= 65535;
+    t.group = many ? n_inputs : 1;
+    t.settings = many ? (int)std::min<long long>(MAX_SETTINGS, LAUNCH_ITEMS / items) : 1;
+    t.batch = many ? t.settings : (int)(BH * s.d * sizeof(float) / tune_slot_bytes(s));   // 5 (d = 64) or 10 (d = 128)
+    size_t off = 0;
+    auto take = [&](size_t bytes) { const size_t o = off; off += align256(bytes); return o; };
+    t.pooled_q = take(n * BH * s.Tm * s.d * sizeof(double));
+    t.ksum_t = take(n * BH * s.Tn * s.d * sizeof(double));
+    t.sim_q = take(n * BH * s.Tm * sizeof(double));
+    t.sim_k = take(n * BH * s.Tn * sizeof(double));
+    t.k_mean = take(n * BH * s.d * sizeof(float));
+    t.logits = take(n * BH * s.Tm * s.Tn * sizeof(double));
+    t.Qq = take(n * BH * s.N * s.d);
+    t.Kq = take(n * BH * s.N * s.d);
+    t.q_scale = take(n * BH * s.Tm * sizeof(float));
+    t.k_scale = take(n * BH * s.Tn * sizeof(float));
+    Shape all = s;
+    all.B = n_inputs * s.B;
+    t.v_tiles = take(v_tiles_layout(all).total);
+    t.o_ref = off;   // [inputs], then o_cur: one packed tensor
+    off += n * BH * s.N * s.d * sizeof(uint16_t);
+    t.o_cur = off;
+    take((size_t)t.settings * t.group * BH * s.N * s.d * sizeof(uint16_t));
+    off = align256(off);
+    t.mask = take((size_t)t.settings * t.group * BH * s.Tm * s.Tn);
+    t.slots = many ? take(tune_slot_bytes(s) * t.batch * n) : t.k_mean;
+    t.queue = take(ATTN_QUEUE_BYTES);
+    t.total = off;
     return t;
 }
 
@@ -597,7 +632,7 @@ int sparge_tune_workspace_bytes(const sparge_desc* desc, int n_inputs, size_t* b
     int rc = check_desc(desc, &s);
     if (rc) return rc;
     if (n_inputs < 1 || !bytes) return fail(SPARGE_EINVAL, "n_inputs must be >= 1 and bytes not NULL");
-    *bytes = tune_layout(s, n_inputs).total;
+    *bytes = std::max(tune_layout(s, n_inputs, false).total, tune_layout(s, n_inputs, true).total);
     return SPARGE_OK;
 }
 
@@ -626,28 +661,20 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
         if (std::isnan(theta_grid[b])) return fail(SPARGE_EINVAL, "theta_grid[%d] is NaN", b);
     for (int c = 0; c < n_lambda; ++c)
         if (!(lambda_grid[c] < 0.f)) return fail(SPARGE_EINVAL, "lambda_grid[%d] must be < 0", c);
-    const TuneWs t = tune_layout(s, n_inputs);
+    TuneWs t = tune_layout(s, n_inputs, false);
     if (!ws) return fail(SPARGE_EINVAL, "workspace is NULL");
     if (reinterpret_cast<uintptr_t>(ws) & 255u) return fail(SPARGE_EINVAL, "workspace must be 256-byte aligned");
+    if (ws_bytes < t.total) t = tune_layout(s, n_inputs, true);   // room for one setting and input at a time
     if (ws_bytes < t.total) return fail(SPARGE_ENOSPACE, "workspace has %zu bytes, %zu needed", ws_bytes, t.total);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const Workspace w = plan(s, SPARGE_WS_FORWARD);
     const int BH = s.B * s.H, H = s.H;
-    auto fwd = [&](int n) { return static_cast<void*>(static_cast<char*>(ws) + t.per_input * n); };
-    auto o_ref = [&](int n) { return static_cast<void*>(static_cast<char*>(ws) + t.per_input * n + t.fwd_bytes); };
-    void* o_cur = at<char>(ws, t.o_cur);
     hipError_t e;
-    AttnStart start;
-    // Settings are enqueued one after the other and read back together: each writes its error sums {2 doubles} and
-    // counters {4 uint64} per (batch, head) into a slot of its input, and the host waits once per batch of slots.  The
-    // slots lie where the K mean was (d floats per (batch, head)), which nothing reads after the quantization.
-    const size_t slot_bytes = (size_t)BH * (2 * sizeof(double) + 4 * sizeof(uint64_t));
-    const int batch = static_cast<int>((size_t)BH * s.d * sizeof(float) / slot_bytes);   // 5 (d = 64) or 10 (d = 128)
+    const size_t slot_bytes = tune_slot_bytes(s);
     const int n1 = n_tau * n_theta;
     std::vector<char> host;                              // the slots of a batch, as read back
     std::vector<double> t1, t2, best_sp, best_err;       // the tables of both stages, the chosen settings
     try {
-        host.resize(slot_bytes * std::min(batch, std::max(n1, n_lambda)) * n_inputs);
+        host.resize(slot_bytes * std::min(t.batch, std::max(n1, n_lambda)) * n_inputs);
         t1.resize((size_t)n1 * H * 2);
         t2.resize((size_t)n_lambda * H * 2);
         best_sp.resize(H);
@@ -655,64 +682,112 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
     } catch (const std::exception&) {
         return fail(SPARGE_ENOSPACE, "no host memory for the search's tables (%d + %d settings)", n1, n_lambda);
     }
+    // operands of input n on
+    const size_t QN = (size_t)BH * s.Tm, KN = (size_t)BH * s.Tn, EL = (size_t)BH * s.N * s.d;   // per input: Q blocks, key blocks, elements
+    auto pooled_q = [&](int n) { return at<double>(ws, t.pooled_q) + n * QN * s.d; };
+    auto ksum_t = [&](int n) { return at<double>(ws, t.ksum_t) + n * KN * s.d; };
+    auto sim_q = [&](int n) { return at<double>(ws, t.sim_q) + n * QN; };
+    auto sim_k = [&](int n) { return at<double>(ws, t.sim_k) + n * KN; };
+    auto k_mean = [&](int n) { return at<float>(ws, t.k_mean) + (size_t)n * BH * s.d; };
+    auto logits = [&](int n) { return at<double>(ws, t.logits) + n * QN * s.Tn; };
+    auto Qq = [&](int n) { return at<int8_t>(ws, t.Qq) + n * EL; };
+    auto Kq = [&](int n) { return at<int8_t>(ws, t.Kq) + n * EL; };
+    auto q_scale = [&](int n) { return at<float>(ws, t.q_scale) + n * QN; };
+    auto k_scale = [&](int n) { return at<float>(ws, t.k_scale) + n * KN; };
+    Shape all = s;
+    all.B = n_inputs * s.B;
+    const VTiles vl = v_tiles_layout(all);
+    auto v_tiles = [&](int n) { return at<char>(ws, t.v_tiles) + n * KN * s.d * BK * (s.pv_fp8 ? 1 : 2); };
+    auto v_scale = [&](int n) { return s.pv_fp8 ? at<float>(ws, t.v_tiles + vl.scale) + (size_t)n * BH * s.d : nullptr; };
+    auto o_ref = [&](int n) { return at<uint16_t>(ws, t.o_ref) + n * EL; };
+    uint16_t* const o_cur = at<uint16_t>(ws, t.o_cur);
+    uint8_t* const mask = at<uint8_t>(ws, t.mask);
+    auto sums_at = [&](int k, int n) { return at<double>(ws, t.slots) + ((size_t)k * n_inputs + n) * BH * 2; };
+    // (counters follow the sums of the k_n settings of a batch)
+    auto counters_at = [&](int k_n, int k, int n) {
+        return reinterpret_cast<uint64_t*>(sums_at(k_n, 0)) + ((size_t)k * n_inputs + n) * BH * 4;
+    };
+    // shape of a launch: `entries` x (batch, head) pairs of the packed outputs on the operands of `inputs` inputs
+    auto launch_shape = [&](int entries, int inputs) {
+        Shape x = s;
+        x.B = entries * s.B;
+        x.sn = s.d, x.sh = (long long)s.N * s.d, x.sb = x.sh * H;
+        x.op_bh = inputs * BH;
+        return x;
+    };
+    // full attention (dense) and / or settings k0 .. k0 + k_n - 1 of a batch of b_n on `inputs` inputs from n on
+    auto attend = [&](bool dense, int k0, int k_n, int b_n, int n, int inputs, bool one_mask, const HeadParams& lp, int by_setting) -> int {
+        Shape x = launch_shape((dense ? inputs : 0) + k_n * inputs, inputs);
+        x.dense_bh = dense ? inputs * BH : 0;
+        x.one_mask = one_mask, x.by_setting = by_setting;
+        uint64_t* counters = k_n ? counters_at(b_n, k0, n) : nullptr;
+        AttnStart start;
+        int r;
+        if ((r = plan_and_set_attn(x, causal, at<void>(ws, t.queue), counters, &start, st))) return r;
+        return timed_attn(Qq(n), Kq(n), q_scale(n), k_scale(n), v_tiles(n), v_scale(n), x, k_n ? mask : nullptr, lp, sm_scale,
+                          causal, dense ? o_ref(n) : o_cur, counters, start, st);
+    };
 
-    // per input, once: block statistics, quantization, V tiles, and the full attention it is measured against
+    // per input, once: block statistics, quantization, V tiles and compressed logits
     HeadParams off;
     std::memset(&off, 0, sizeof(off));
-    for (int h = 0; h < H; ++h) off.v[h] = -INFINITY;
+    for (int h = 0; h < SPARGE_MAX_HEADS; ++h) off.v[h] = -INFINITY;
     for (int n = 0; n < n_inputs; ++n) {
-        void* f = fwd(n);
-        if ((rc = run_stats_and_quant(Q[n], K[n], s, at<double>(f, w.pooled_q), at<double>(f, w.ksum_t),
-                                      at<double>(f, w.sim_q), at<double>(f, w.sim_k), at<int8_t>(f, w.Qq),
-                                      at<float>(f, w.q_scale), at<int8_t>(f, w.Kq), at<float>(f, w.k_scale),
-                                      at<float>(f, w.k_mean), AttnStart{}, st))) return rc;
-        if ((rc = plan_and_set_attn(s, causal, at<void>(f, w.queue), nullptr, &start, st))) return rc;
-        if ((rc = run_attn(at<int8_t>(f, w.Qq), at<int8_t>(f, w.Kq), at<float>(f, w.q_scale), at<float>(f, w.k_scale),
-                           V[n], s, at<char>(f, w.v_tiles), nullptr, off, sm_scale, causal, o_ref(n), nullptr,
-                           start, st)))
-            return rc;
-        // the compressed logits are the same for every setting
-        if ((e = launch_logits(at<double>(f, w.pooled_q), at<double>(f, w.ksum_t), s, sm_scale, causal, at<double>(f, w.logits),
-                               st)) !=
-            hipSuccess) return hip_fail(e, "logits");
+        const bool tiles_too = short_call(s) && !s.pv_fp8;
+        e = short_call(s) ? launch_prep(Q[n], K[n], V[n], s, pooled_q(n), ksum_t(n), sim_q(n), sim_k(n), Qq(n), q_scale(n),
+                                        tiles_too ? reinterpret_cast<uint16_t*>(v_tiles(n)) : nullptr, AttnStart{}, st)
+                          : launch_block_stats(Q[n], K[n], s, pooled_q(n), ksum_t(n), sim_q(n), sim_k(n), Qq(n), q_scale(n),
+                                               AttnStart{}, st);
+        if (e != hipSuccess) return hip_fail(e, "block statistics");
+        if (s.pv_fp8)
+            e = launch_v_tiles_fp8(V[n], s, reinterpret_cast<unsigned char*>(v_tiles(n)), const_cast<float*>(v_scale(n)),
+                                   at<uint32_t>(ws, t.v_tiles + vl.amax) + (size_t)n * BH * s.d, st);
+        else if (!tiles_too)
+            e = launch_v_tiles(V[n], s, reinterpret_cast<uint16_t*>(v_tiles(n)), st);
+        if (e != hipSuccess) return hip_fail(e, "v_tiles");
     }
+    for (int n = 0; n < n_inputs; n += t.group) {
+        const Shape x = launch_shape(t.group, t.group);
+        if ((e = launch_k_mean(ksum_t(n), x, k_mean(n), st)) != hipSuccess) return hip_fail(e, "k_mean");
+        if ((e = launch_logits(pooled_q(n), ksum_t(n), x, sm_scale, causal, logits(n), st)) != hipSuccess) return hip_fail(e, "logits");
+    }
+    for (int n = 0; n < n_inputs; ++n)
+        if ((e = launch_quant_k(K[n], s, k_mean(n), Kq(n), k_scale(n), st)) != hipSuccess) return hip_fail(e, "quant_k");
 
-    auto slot = [&](int n, int k) { return at<char>(fwd(n), w.k_mean) + k * slot_bytes; };
-    auto enqueue = [&](const HeadParams& tp, const HeadParams& thp, const HeadParams& lp, int k) -> int {
-        for (int n = 0; n < n_inputs; ++n) {
-            void* f = fwd(n);
-            double* sums = reinterpret_cast<double*>(slot(n, k));
-            uint64_t* counters = reinterpret_cast<uint64_t*>(sums + 2 * BH);
+    // the k_n settings from k0 on of a batch of b_n; tp, thp: one value per setting (stage 1, with the full attention in
+    // front the first time) or per head, the same mask for all of them (stage 2)
+    auto run = [&](bool stage1, bool dense, const HeadParams& tp, const HeadParams& thp, const HeadParams& lp, int k0, int k_n, int b_n) -> int {
+        for (int n = 0; n < n_inputs; n += t.group) {
+            const int G = t.group;
             int r;
-            if ((e = launch_topcdf(at<double>(f, w.logits), at<double>(f, w.sim_q), at<double>(f, w.sim_k), s, tp, thp, causal,
-                                   at<uint8_t>(f, w.mask), st)) != hipSuccess) return hip_fail(e, "topcdf");
-            if ((r = plan_and_set_attn(s, causal, at<void>(f, w.queue), counters, &start, st))) return r;
-            if ((r = timed_attn(at<int8_t>(f, w.Qq), at<int8_t>(f, w.Kq), at<float>(f, w.q_scale),
-                                at<float>(f, w.k_scale), at<char>(f, w.v_tiles), s, at<uint8_t>(f, w.mask), lp,
-                                sm_scale, causal, o_cur, counters, start, st))) return r;
-            if ((e = launch_rel_l1(o_cur, o_ref(n), s, sums, st)) != hipSuccess) return hip_fail(e, "rel_l1");
+            if (dense && G < n_inputs && (r = attend(true, 0, 0, 0, n, G, false, off, 0))) return r;
+            Shape x = launch_shape((stage1 ? k_n : 1) * G, G);
+            x.by_setting = stage1;
+            if ((e = launch_topcdf(logits(n), sim_q(n), sim_k(n), x, tp, thp, causal, mask, st)) != hipSuccess) return hip_fail(e, "topcdf");
+            if ((r = attend(dense && G == n_inputs, k0, k_n, b_n, n, G, !stage1, lp, !stage1))) return r;
+            x = launch_shape(k_n * G, G);
+            if ((e = launch_rel_l1(o_cur, o_ref(n), x, sums_at(k0, n), st)) != hipSuccess) return hip_fail(e, "rel_l1");
         }
         return SPARGE_OK;
     };
-    // the first k_n slots of every input -> per setting and head the mean sparsity and the worst relative L1
+    // the slots of k_n settings -> per setting and head the mean sparsity and the worst relative L1
     auto collect = [&](int k_n, double* sp_err) -> int {
-        const size_t bytes = slot_bytes * k_n;
-        for (int n = 0; n < n_inputs; ++n)
-            if ((e = hipMemcpyAsync(host.data() + n * bytes, slot(n, 0), bytes, hipMemcpyDeviceToHost, st)) != hipSuccess)
-                return hip_fail(e, "copy error sums and counters");
+        if ((e = hipMemcpyAsync(host.data(), at<char>(ws, t.slots), slot_bytes * k_n * n_inputs, hipMemcpyDeviceToHost, st)) != hipSuccess)
+            return hip_fail(e, "copy error sums and counters");
         if ((e = hipStreamSynchronize(st)) != hipSuccess) return hip_fail(e, "synchronize");
+        const char* const counters = host.data() + (size_t)k_n * n_inputs * BH * 2 * sizeof(double);
         for (int k = 0; k < k_n; ++k)
             for (int h = 0; h < H; ++h) {
                 double sp = 0.0, err = 0.0;
                 for (int n = 0; n < n_inputs; ++n) {
-                    const char* base = host.data() + n * bytes + k * slot_bytes;
                     double num = 0.0, den = 0.0;
                     uint64_t c[4] = {0, 0, 0, 0};
                     for (int b = 0; b < s.B; ++b) {
+                        const size_t at_ = ((size_t)k * n_inputs + n) * BH + b * H + h;
                         double m[2];
                         uint64_t x[4];
-                        std::memcpy(m, base + (size_t)(b * H + h) * sizeof(m), sizeof(m));
-                        std::memcpy(x, base + (size_t)BH * sizeof(m) + (size_t)(b * H + h) * sizeof(x), sizeof(x));
+                        std::memcpy(m, host.data() + at_ * sizeof(m), sizeof(m));
+                        std::memcpy(x, counters + at_ * sizeof(x), sizeof(x));
                         num += m[0];
                         den += m[1];
                         for (int q = 0; q < 4; ++q) c[q] += x[q];
@@ -730,16 +805,17 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
     HeadParams tp, thp, lp;
     std::memset(&tp, 0, sizeof(tp));
     std::memset(&thp, 0, sizeof(thp));
-    for (int k0 = 0; k0 < n1; k0 += batch) {
-        const int k_n = std::min(batch, n1 - k0);
-        for (int k = 0; k < k_n; ++k) {
-            for (int h = 0; h < H; ++h) {
-                tp.v[h] = tau_grid[(k0 + k) / n_theta];
-                thp.v[h] = theta_grid[(k0 + k) % n_theta];
+    for (int c0 = 0; c0 < n1; c0 += t.batch) {
+        const int b_n = std::min(t.batch, n1 - c0);
+        for (int k0 = 0; k0 < b_n; k0 += t.settings) {
+            const int k_n = std::min(t.settings, b_n - k0);
+            for (int k = 0; k < k_n; ++k) {
+                tp.v[k] = tau_grid[(c0 + k0 + k) / n_theta];
+                thp.v[k] = theta_grid[(c0 + k0 + k) % n_theta];
             }
-            if ((rc = enqueue(tp, thp, off, k))) return rc;
+            if ((rc = run(true, c0 + k0 == 0, tp, thp, off, k0, k_n, b_n))) return rc;
         }
-        if ((rc = collect(k_n, &t1[(size_t)k0 * H * 2]))) return rc;
+        if ((rc = collect(b_n, &t1[(size_t)c0 * H * 2]))) return rc;
     }
     for (int h = 0; h < H; ++h) {
         int best = -1;
@@ -764,13 +840,14 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
 
     // stage 2: the lambda grid at each head's own (tau, theta)
     std::memset(&lp, 0, sizeof(lp));
-    for (int c0 = 0; c0 < n_lambda; c0 += batch) {
-        const int k_n = std::min(batch, n_lambda - c0);
-        for (int k = 0; k < k_n; ++k) {
-            for (int h = 0; h < H; ++h) lp.v[h] = lambda_grid[c0 + k];
-            if ((rc = enqueue(tp, thp, lp, k))) return rc;
+    for (int c0 = 0; c0 < n_lambda; c0 += t.batch) {
+        const int b_n = std::min(t.batch, n_lambda - c0);
+        for (int k0 = 0; k0 < b_n; k0 += t.settings) {
+            const int k_n = std::min(t.settings, b_n - k0);
+            for (int k = 0; k < k_n; ++k) lp.v[k] = lambda_grid[c0 + k0 + k];
+            if ((rc = run(false, false, tp, thp, lp, k0, k_n, b_n))) return rc;
         }
-        if ((rc = collect(k_n, &t2[(size_t)c0 * H * 2]))) return rc;
+        if ((rc = collect(b_n, &t2[(size_t)c0 * H * 2]))) return rc;
     }
     if (stage2 && n_lambda) std::memcpy(stage2, t2.data(), t2.size() * sizeof(double));
     for (int c = 0; c < n_lambda; ++c)

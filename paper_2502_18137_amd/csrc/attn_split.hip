@@ -92,6 +92,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     const int bh = work / n_rg;
     const int g = CAUSAL ? n_rg - 1 - work % n_rg : work % n_rg;
     const int b = bh / s.H, h = bh % s.H, i = g / (BQ / RG);
+    const int op = s.operand(bh), own = bh - s.dense_bh;   // (Shape: settings of one launch)
     const int lane = threadIdx.x & 63, l32 = lane & 31, hl = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int qrow = g * RG + l32;
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
             qf[st] = QK16 ? *reinterpret_cast<const v4i*>(static_cast<const uint16_t*>(a.Qp) + b * s.sb + h * s.sh +
                                                           (long long)qrow * s.sn + st * 16 + hl * 8)
                           : *reinterpret_cast<const v4i*>(static_cast<const int8_t*>(a.Qp) +
-                                                          ((long long)bh * s.N + qrow) * D + st * 32 + hl * 16);
+                                                          ((long long)op * s.N + qrow) * D + st * 32 + hl * 16);
     }
     // ---- the Q block's kept key blocks in ascending order: every wave counts all of them, the first four write a quarter.
     // A causal group runs only the tiles it sees (the other ones of its block change nothing).
@@ -115,13 +116,13 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     {
         unsigned int mk[NW] = {1, 1, 1, 1};
         static_assert(SPLIT_MAX_TN == 64 * NW, "one flag per lane and wave");
-        if (a.mask) {   // (loads without conditions: all in flight together)
-            const uint8_t* mrow = a.mask + ((long long)bh * s.Tm + i) * s.Tn;
+        if (a.mask && own >= 0) {   // (loads without conditions: all in flight together)
+            const uint8_t* mrow = a.mask + ((long long)(s.one_mask ? op : own) * s.Tm + i) * s.Tn;
 #pragma unroll
             for (int q = 0; q < NW; ++q) mk[q] = mrow[min(q * 64 + lane, jmax - 1)];
         }
-        const float sc = QK16 ? 1.f : a.k_scale[(long long)bh * s.Tn + min((wave & (NW - 1)) * 64 + lane, jmax - 1)];
-        const float qs = (QK16 ? 1.f : a.q_scale[(long long)bh * s.Tm + i]) * a.sm_scale * LOG2E;
+        const float sc = QK16 ? 1.f : a.k_scale[(long long)op * s.Tn + min((wave & (NW - 1)) * 64 + lane, jmax - 1)];
+        const float qs = (QK16 ? 1.f : a.q_scale[(long long)op * s.Tm + i]) * a.sm_scale * LOG2E;
 #pragma unroll
         for (int q = 0; q < NW; ++q) {
             const int j = q * 64 + lane;
@@ -139,7 +140,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     if (wave == NW && lane < 4 * NW) jl[listed + lane] = 0;   // copies behind the list fetch a tile nobody reads
     lds_barrier();
 
-    const float lam2 = a.lambda_h.v[h] * LOG2E;
+    const float lam2 = a.lambda_h.v[s.param(own, h)] * LOG2E;
     float m_true = NEG, m_ref = NEG;
     // what both kinds of waves follow: the running maximum through the round's tiles (ml: their row maxima) ...
     float ml[NW], m[NW];
@@ -260,8 +261,8 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
             sc = sc_next;
             if (KB == 2) buf ^= 1;
         }
-        if (a.stats && threadIdx.x == 0) {   // row groups whose last row sees the key block; tiles once per Q block
-            unsigned long long* st = a.stats + bh * 4;
+        if (a.stats && own >= 0 && threadIdx.x == 0) {   // row groups whose last row sees the key block; tiles once per Q block
+            unsigned long long* st = a.stats + own * 4;
             atomicAdd(&st[3], (unsigned long long)(CAUSAL ? min(jmax, (min(g * RG + RG, s.N) - 1) / BK + 1) : jmax));
             if (g % (BQ / RG) == 0) {
                 atomicAdd(&st[0], (unsigned long long)listed);
@@ -276,7 +277,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     constexpr int K_TILES = D == 128 ? 1 : 2;
     const int k_tile0 = D == 128 ? hw : 2 * (hw - NDT);
     const unsigned char* kbase = static_cast<const unsigned char*>(a.Kp) +
-                                 (QK16 ? 2 * (b * s.sb + h * s.sh) : (long long)bh * s.N * D);
+                                 (QK16 ? 2 * (b * s.sb + h * s.sh) : (long long)op * s.N * D);
     const int k_rowg = QK16 ? static_cast<int>(2 * s.sn) : D;  // bytes between K rows in memory
     // 16-byte chunks are XOR-ed on the memory side of a copy as the operand reads expect
     const int k_row = lane / K_CPR, k_phys = lane % K_CPR;
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     }
 
     // ---- product waves
-    const unsigned char* vbase = a.v_tiles + (long long)bh * s.Tn * V_BYTES + hw * (VT_DMA * 1024);
+    const unsigned char* vbase = a.v_tiles + (long long)op * s.Tn * V_BYTES + hw * (VT_DMA * 1024);
     const uint32_t v_lds = lds_address(Vs[hw][0]);
     uint32_t v_src[VT_DMA];
 #pragma unroll
@@ -457,7 +458,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
         for (int q4 = 0; q4 < 4; ++q4) {
             const int c0 = hw * 32 + 8 * q4 + 4 * hl;
             float4 dv = make_float4(1.f, 1.f, 1.f, 1.f);  // FP8: the channels' V scales
-            if (FP8) dv = *reinterpret_cast<const float4*>(a.v_scale + (long long)bh * D + c0);
+            if (FP8) dv = *reinterpret_cast<const float4*>(a.v_scale + (long long)op * D + c0);
             const float dvs[4] = {dv.x, dv.y, dv.z, dv.w};
             uint16_t o[4];
 #pragma unroll
@@ -468,7 +469,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
             *reinterpret_cast<uint2*>(orow + c0) = wd;
         }
     }
-    if (a.stats && hw == 0 && lane == 0 && pv_done) atomicAdd(&a.stats[bh * 4 + 1], (unsigned long long)pv_done);
+    if (a.stats && own >= 0 && hw == 0 && lane == 0 && pv_done) atomicAdd(&a.stats[own * 4 + 1], (unsigned long long)pv_done);
 }
 
 }  // namespace

@@ -18,6 +18,16 @@ struct Shape {
     int Tm, Tn;
     int pv_fp8;            // P~V product in FP8 (E4M3) instead of the tensors' 16-bit type
     int qk16;              // Q K^T product on the 16-bit tensors themselves instead of their INT8 quantization
+    // Several settings of the same operands in one launch (the hyper-parameter search): (batch, head) pairs beyond op_bh
+    // use the operands of those before them, pair by pair.  The first dense_bh pairs keep every block and count nothing;
+    // mask and counters begin behind them.
+    int op_bh;             // (batch, head) pairs that have operands of their own; an ordinary call: B H
+    int dense_bh;
+    int by_setting;        // the per-head parameters (tau, theta, lambda) are one value per setting instead
+    int one_mask;          // the mask has op_bh pairs: one for all settings
+
+    __host__ __device__ int operand(int bh) const { return bh < op_bh ? bh : bh % op_bh; }
+    __host__ __device__ int param(int own, int h) const { return by_setting ? own / op_bh : h; }   // own: pair behind the dense ones
 };
 
 // Per-head scalars travel to the device inside the kernel argument block.

@@ -118,14 +118,15 @@ __global__ __launch_bounds__(256) void topcdf_kernel(const double* __restrict__ 
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const long long bh = (long long)b * s.H + h;
     const int tid = threadIdx.x;
-    const double tau = static_cast<double>(tau_h.v[h]);
-    const double theta = static_cast<double>(theta_h.v[h]);
-    const double* row = logits + (bh * s.Tm + i) * s.Tn;
-    const double* sk = sim_k + bh * s.Tn;
+    const int op = s.operand(static_cast<int>(bh)), par = s.param(static_cast<int>(bh), h);   // (Shape: settings of one launch)
+    const double tau = static_cast<double>(tau_h.v[par]);
+    const double theta = static_cast<double>(theta_h.v[par]);
+    const double* row = logits + ((long long)op * s.Tm + i) * s.Tn;
+    const double* sk = sim_k + (long long)op * s.Tn;
     const double NEG = -__builtin_inf();
 
     // A query block that is not self-similar keeps every (visible) key block: nothing to rank.
-    if (sim_q[bh * s.Tm + i] < theta) {
+    if (sim_q[(long long)op * s.Tm + i] < theta) {
         uint8_t* out_row = mask + (bh * s.Tm + i) * s.Tn;
         for (int j = tid; j < s.Tn; j += 256) out_row[j] = (causal && j * BK > i * BQ + (BQ - 1)) ? 0 : 1;
         return;
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(256) void topcdf_kernel(const double* __restrict__ 
     __syncthreads();
 
     // 5. fix-block overrides and causal rules, then the row goes out
-    const bool fix_q = sim_q[bh * s.Tm + i] < theta;
+    const bool fix_q = sim_q[(long long)op * s.Tm + i] < theta;
     uint8_t* out = mask + (bh * s.Tm + i) * s.Tn;
     for (int j = tid; j < s.Tn; j += 256) {
         uint8_t m = flag[j];
@@ -519,9 +520,11 @@ __global__ __launch_bounds__(256) void topcdf_wave_kernel(const double* __restri
     if (rowid >= n_rows) return;
     const int i = rowid % s.Tm;
     const long long bh = rowid / s.Tm;
-    const int h = static_cast<int>(bh % s.H);
-    const double* row = logits + (long long)rowid * s.Tn;
-    topcdf_row_of<EPL>([&](int j) { return row[j]; }, i, sim_q[rowid], sim_k + bh * s.Tn, s, static_cast<double>(tau_h.v[h]),
+    const int op = s.operand(static_cast<int>(bh));   // (Shape: settings of one launch)
+    const int h = s.param(static_cast<int>(bh), static_cast<int>(bh % s.H));
+    const long long op_row = (long long)op * s.Tm + i;
+    const double* row = logits + op_row * s.Tn;
+    topcdf_row_of<EPL>([&](int j) { return row[j]; }, i, sim_q[op_row], sim_k + (long long)op * s.Tn, s, static_cast<double>(tau_h.v[h]),
                     static_cast<double>(theta_h.v[h]), causal, lane, pval[wave], flag[wave],
                     mask + (long long)rowid * s.Tn);
 }

@@ -137,3 +137,33 @@ def test_grids_of_several_batches_equal_searches_of_single_settings(sp, d, pv_fp
         for c, lam in enumerate(lams):
             one = sp.sparge_tune(inputs, [got["tau"][h]], [got["theta"][h]], [lam], 0.06, 0.08, pv_fp8=pv_fp8)
             assert np.array_equal(got["stage2"][c, h], one["stage2"][0, h]), (h, lam)
+
+
+@pytest.mark.parametrize("B,H,N,d,causal,pv_fp8", [(1, 2, 640, 64, False, False), (2, 3, 333, 128, True, False),
+                                                   (1, 4, 1100, 64, True, True), (3, 1, 64, 128, False, False)])
+def test_settings_of_one_launch_equal_settings_one_by_one(sp, B, H, N, d, causal, pv_fp8, monkeypatch):
+    """A small search runs all inputs and up to 16 settings in one launch when the workspace has room for their outputs and
+    masks, and one setting on one input at a time when it has not: the same tables and choices, bit for bit."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(N)
+    draw = lambda: (torch.randn(B, H, (N + 127) // 128, d, generator=g, device="cuda").repeat_interleave(128, 2)[:, :, :N]
+                    + 0.5 * torch.randn(B, H, N, d, generator=g, device="cuda")).to(torch.bfloat16)
+    inputs = [tuple(draw() for _ in range(3)) for _ in range(3)]
+    grids = ([0.5, 0.7, 0.9], [-0.5, 0.2, 0.4, 0.6, 0.8, 0.9], [-10.0 + 0.5 * n for n in range(18)])   # 18 settings in each stage
+    print(f"B={B} H={H} N={N} d={d} causal={causal} pv_fp8={pv_fp8}", flush=True)
+    whole = sp.sparge_tune(inputs, *grids, 0.2, 0.25, causal=causal, pv_fp8=pv_fp8)
+    empty, ran = torch.empty, 0
+    for part in (0.9, 0.7, 0.5, 0.3):
+        monkeypatch.setattr(torch, "empty", lambda n, **k: empty(int(n * part), **k))
+        try:
+            got = sp.sparge_tune(inputs, *grids, 0.2, 0.25, causal=causal, pv_fp8=pv_fp8)
+        except sp.SpargeError as err:
+            assert "workspace" in str(err)
+            break
+        finally:
+            monkeypatch.undo()
+        ran += 1
+        assert np.array_equal(got["stage1"], whole["stage1"]) and np.array_equal(got["stage2"], whole["stage2"]), part
+        assert all(got[k] == whole[k] for k in ("tau", "theta", "lam", "sparsity", "l1")), part
+    assert ran > 0
+    assert N < 300 or len(np.unique(whole["stage1"][..., 0, 0])) > 3      # (a single key block is always kept)
