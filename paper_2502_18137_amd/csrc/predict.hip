@@ -1,7 +1,7 @@
 // Stage-1 predictor after the block statistics (Alg. 1 lines 5-6; Sec. 3.2):
 //   logits : S_hat = sm_scale * q k^T on the pooled tokens, fp64 (tiny next to the attention itself)
-//   topcdf : per mask row: -inf columns, softmax, TopCdf(tau) by an in-LDS bitonic sort and a
-//            prefix sum, fix-block overrides, causal rules.
+//   topcdf : per mask row: -inf columns, softmax, TopCdf(tau) by bracketing the cut in the ranking (rows beyond
+//            2048 key blocks: by an in-LDS bitonic sort and a prefix sum), fix-block overrides, causal rules.
 //   short calls: both in one launch, beside the K quantization (predict_quant_kernel).
 // All arithmetic is fp64 so that block decisions agree with an fp64 reference except for
 // statistics that sit within ~1e-13 of a threshold.
@@ -22,6 +22,11 @@ __device__ __forceinline__ double shfl_up_f64(double v, int delta) {
     lo = __shfl_up(lo, delta);
     hi = __shfl_up(hi, delta);
     return __hiloint2double(hi, lo);
+}
+
+// A wave-uniform fp64 value, moved to scalar registers.
+__device__ __forceinline__ double uniform_f64(double v) {
+    return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)), __builtin_amdgcn_readfirstlane(__double2loint(v)));
 }
 
 // Key blocks that mask row i has to rank: all of them, or (causal) those up to the end of its own Q block.
@@ -255,116 +260,6 @@ __global__ __launch_bounds__(256) void topcdf_kernel(const double* __restrict__ 
     }
 }
 
-// v_permlane16_swap (LD = 16: odd rows of 16 lanes of a against even rows of b) or v_permlane32_swap (LD = 32:
-// upper half of a against lower half of b); applying it twice restores a and b
-template <int LD>
-__device__ __forceinline__ void lane_swap(uint32_t a, uint32_t b, uint32_t& a_out, uint32_t& b_out) {
-    static_assert(LD == 16 || LD == 32, "no such swap");
-    if constexpr (LD == 16) {
-        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-        a_out = r[0], b_out = r[1];
-    } else {
-        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-        a_out = r[0], b_out = r[1];
-    }
-}
-
-// Bitonic sort, descending, of 64 * EPL keys held EPL consecutive ranks per lane.  The stages are
-// instantiated one by one (K: length of the runs being merged, JJ: distance of the pairs), so that every
-// register index, DPP control and swap is a compile-time constant.
-// max / min of two keys read as fp64 numbers: two instructions for a compare-exchange where the 64-bit integer
-// comparison and its four selects take five.  The keys are never NaN or infinite (probabilities <= 1 with an index
-// in the low mantissa bits, or 0), fp64 denormals are not flushed, and the instructions are written out so that
-// the compiler does not canonicalize their inputs first.
-__device__ __forceinline__ void max_min_f64(unsigned long long a, unsigned long long b, unsigned long long& hi,
-                                            unsigned long long& lo) {
-    const double x = __longlong_as_double(static_cast<long long>(a)), y = __longlong_as_double(static_cast<long long>(b));
-    double mx, mn;
-    asm("v_max_f64 %0, %1, %2" : "=v"(mx) : "v"(x), "v"(y));
-    asm("v_min_f64 %0, %1, %2" : "=v"(mn) : "v"(x), "v"(y));
-    hi = static_cast<unsigned long long>(__double_as_longlong(mx));
-    lo = static_cast<unsigned long long>(__double_as_longlong(mn));
-}
-
-// Runs of K >= EPL ranks ascend or descend by lane.  While such runs are merged, the lanes of ascending runs carry
-// their keys with the sign bit set (set_run_sign, once per run length): read as fp64 the keys of every lane then
-// descend the same way, and a pair inside a lane is ordered by max / min without a select.  The comparisons
-// between lanes keep reading the keys as integers; both keys of such a pair carry the same sign bit, so their
-// integer order is the order of the keys themselves.  The last run descends in every lane: the signs end up clear.
-template <int EPL, int K>
-__device__ __forceinline__ void set_run_sign(unsigned long long (&key)[EPL], int lane) {
-    if constexpr (K >= EPL) {
-        const unsigned long long sign = (((lane * EPL) & K) == 0) ? 0ull : 0x8000000000000000ull;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) key[e] = (key[e] & 0x7FFFFFFFFFFFFFFFull) | sign;
-    }
-}
-
-template <int EPL, int K, int JJ>
-__device__ __forceinline__ void bitonic_stage(unsigned long long (&key)[EPL], int lane) {
-    if constexpr (JJ < EPL) {  // both members of a pair in this lane
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-            if (e & JJ) continue;
-            unsigned long long hi, lo;
-            max_min_f64(key[e], key[e | JJ], hi, lo);
-            // short runs: the direction is known per register; long runs: the sign bits make every lane descend
-            const bool desc = K < EPL ? ((e & K) == 0) : true;
-            key[e] = desc ? hi : lo;
-            key[e | JJ] = desc ? lo : hi;
-        }
-    } else {
-        constexpr int LD = JJ / EPL;  // partner lane = lane ^ LD
-        const bool desc = ((lane * EPL) & K) == 0;
-        if constexpr (LD >= 16) {
-            // Lanes 16 or 32 apart: the lane swap of the keys of two entries e, e+1 puts both members of a pair
-            // into one lane (one half of the lanes gets the pairs of entry e, the other half those of entry
-            // e+1, earlier rank first); the pair is ordered there like a pair inside a lane, and the same swap
-            // takes the keys home.
-#pragma unroll
-            for (int e = 0; e < EPL; e += 2) {
-                uint32_t al, ah, bl, bh;
-                lane_swap<LD>(static_cast<uint32_t>(key[e]), static_cast<uint32_t>(key[e + 1]), al, bl);
-                lane_swap<LD>(static_cast<uint32_t>(key[e] >> 32), static_cast<uint32_t>(key[e + 1] >> 32), ah, bh);
-                const unsigned long long a = (static_cast<unsigned long long>(ah) << 32) | al;
-                const unsigned long long b = (static_cast<unsigned long long>(bh) << 32) | bl;
-                const bool exch = (a > b) != desc;
-                const unsigned long long first = exch ? b : a, second = exch ? a : b;
-                lane_swap<LD>(static_cast<uint32_t>(first), static_cast<uint32_t>(second), al, bl);
-                lane_swap<LD>(static_cast<uint32_t>(first >> 32), static_cast<uint32_t>(second >> 32), ah, bh);
-                key[e] = (static_cast<unsigned long long>(ah) << 32) | al;
-                key[e + 1] = (static_cast<unsigned long long>(bh) << 32) | bl;
-            }
-        } else {
-            // closer lanes: the partner's key comes through DPP moves
-            const bool upper = (lane & LD) != 0;  // this lane holds the later ranks of the pairs
-            // the earlier rank of a pair keeps the larger key when the run descends, the later rank the smaller:
-            // take the partner's key if it is larger and the larger one is wanted, or neither (equal keys are
-            // padding, either copy will do)
-            const bool want_min = desc == upper;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) {
-                const unsigned long long mine = key[e];
-                const uint32_t plo = row_xchg<LD>(static_cast<uint32_t>(mine));
-                const uint32_t phi = row_xchg<LD>(static_cast<uint32_t>(mine >> 32));
-                const unsigned long long other = (static_cast<unsigned long long>(phi) << 32) | plo;
-                key[e] = ((other > mine) != want_min) ? other : mine;
-            }
-        }
-    }
-}
-template <int EPL, int K, int JJ>
-__device__ __forceinline__ void bitonic_merge(unsigned long long (&key)[EPL], int lane) {
-    bitonic_stage<EPL, K, JJ>(key, lane);
-    if constexpr (JJ > 1) bitonic_merge<EPL, K, JJ / 2>(key, lane);
-}
-template <int EPL, int K = 2>
-__device__ __forceinline__ void bitonic_sort(unsigned long long (&key)[EPL], int lane) {
-    set_run_sign<EPL, K>(key, lane);
-    bitonic_merge<EPL, K, K / 2>(key, lane);
-    if constexpr (K < 64 * EPL) bitonic_sort<EPL, 2 * K>(key, lane);
-}
-
 // maximum over the wave (every lane gets it)
 template <int PARTNER>
 __device__ __forceinline__ double max_of_partner(double v) {
@@ -388,121 +283,145 @@ __device__ __forceinline__ double wave_max(double v) {
     return max_of_partner<32>(v);
 }
 
-// TopCdf of one mask row by one wave, the sort in registers: lane L holds the EPL consecutive ranks
-// L * EPL .. L * EPL + EPL - 1 as 64-bit keys (see topcdf_kernel for the key).  A bitonic stage at a distance
-// below EPL exchanges inside a lane (compile-time register indices), a larger one takes the partner
-// lane's key with DPP moves or lane swaps (vector ALU: with ds_bpermute the LDS pipeline was the limit);
-// nothing but the final flags and the exact probabilities goes through LDS, and no workgroup barrier is needed.  Same comparisons, hence the same order, as the LDS version.
+// TopCdf of one mask row by one wave, without sorting the row: an entry is kept if the mass ranked before it is below
+// the threshold, so one cut in the ranking decides the row.  Keys (see topcdf_kernel) rank the entries by one 64-bit
+// comparison; lane L holds those of key blocks 64 e + L.  The cut is bracketed between two keys -- the mass from `lo` on
+// reaches the threshold, the mass from `hi` on does not -- and the bracket halved until at most FEW entries lie in it; those
+// are ranked one by one.  Keys differ, so that ends after at most 64 halvings; the first probe is the smallest
+// probability the cut can have when nothing else is known (all that ranks from the cut on is more than (1 - tau) of the
+// mass), which leaves the few octaves below the row's maximum.
+// What bounds it is the vector ALU (16 rows a SIMD at 32 x 65536): a probe costs EPL comparisons, selections and fp64
+// additions a lane and one reduction, five to eight of them a row, where a bitonic sort of the row in registers
+// ran 55 stages at EPL = 16: 60 against 151 us at 32 x 65536, 26 against 43 us at 48 x 17550 (EPL = 8), 29 against
+// 84 us at 32 x 32768 causal; no difference where the launch is one wave's latency (EPL = 2, 4).
 // The ranks cover the n key blocks that the row sees (n <= 64 EPL); the others are 0 in the mask.
-// row_at(j): the row's logit of key block j < n; pval, flag: 64 * EPL entries of LDS of this wave's own (pval may be
-// where row_at reads from: all logits are read before the first probability is written).
+// row_at(j): the row's logit of key block j < n; cand: 2 FEW doubles of LDS of this wave's own (may be where row_at reads
+// from: all logits are read before the first candidate is written).
+constexpr int FEW = 32;
 template <int EPL, class RowAt>
 __device__ __forceinline__ void topcdf_row(RowAt row_at, const int i, const double sim_q_i, const double* __restrict__ sk,
                                            const Shape& s, const double tau, const double theta, const int causal,
-                                           const int n, const int lane, double* pval, uint8_t* flag,
-                                           uint8_t* __restrict__ out) {
+                                           const int n, const int lane, double* cand, uint8_t* __restrict__ out) {
+    typedef unsigned long long u64;
     const double NEG = -__builtin_inf();
     if (sim_q_i < theta) {   // a query block that is not self-similar keeps every visible key block
         for (int j = lane; j < s.Tn; j += 64) out[j] = j < n ? 1 : 0;
         return;
     }
-    // 1.-2. masked logits, softmax, probabilities (entries lane * EPL + e: a lane reads one contiguous piece)
-    double x[EPL];
+    // 1.-2. masked logits, softmax, probabilities (entry e of a lane: key block 64 e + lane)
+    double p[EPL];
+    unsigned int fix = 0;   // bit e: the key block is not self-similar (kept whatever its rank)
     double mx = NEG;
 #pragma unroll
+    for (int e = 0; e < EPL; ++e) {   // (loads without conditions: all in flight together)
+        const int j = min(64 * e + lane, n - 1);
+        p[e] = row_at(j);
+        fix |= static_cast<unsigned int>(sk[j] < theta) << e;
+    }
+#pragma unroll
     for (int e = 0; e < EPL; ++e) {
-        const int j = lane * EPL + e;
-        x[e] = NEG;
-        if (j < n) {
-            x[e] = row_at(j);
-            if (sk[j] < theta) x[e] = NEG;
-        }
-        mx = fmax(mx, x[e]);
+        if (64 * e + lane >= n || (fix >> e & 1)) p[e] = NEG;
+        mx = fmax(mx, p[e]);
     }
     mx = wave_max(mx);
     double z = 0.0;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-        x[e] = (x[e] == NEG) ? 0.0 : exp(x[e] - mx);
-        z += x[e];
+        p[e] = (p[e] == NEG) ? 0.0 : exp(p[e] - mx);
+        z += p[e];
     }
     z = group_sum<64>(z);
     // (one division per lane; x * (1 / z) is within two roundings of x / z, far inside the band in which a
     // TopCdf decision counts as undecided)
     const double rz = z > 0.0 ? 1.0 / z : 0.0;
     double tot = 0.0;
-    unsigned long long key[EPL];
+    u64 key[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-        const int j = lane * EPL + e;
-        const double p = j < n ? x[e] * rz : 0.0;
-        tot += p;
-        pval[j] = p;
-        flag[j] = 0;
-        key[e] = j < n ? ((static_cast<unsigned long long>(__double_as_longlong(p)) & ~0xFFFFull) |
-                             static_cast<unsigned long long>(0xFFFF - j))
-                          : 0ull;   // padding ranks last
+        const int j = 64 * e + lane;
+        p[e] *= rz;
+        tot += p[e];
+        key[e] = j < n ? ((static_cast<u64>(__double_as_longlong(p[e])) & ~0xFFFFull) | static_cast<u64>(0xFFFF - j))
+                       : 0ull;   // below every key
     }
-    tot = group_sum<64>(tot);
-
-    // 3. bitonic sort, descending by key
-    bitonic_sort<EPL>(key, lane);
-
-    // 4. exclusive prefix mass per rank (exact probabilities by index); rank kept iff mass before it < tau * total
-    double pv[EPL];
-    double local = 0.0;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        pv[e] = key[e] ? pval[0xFFFF - static_cast<int>(key[e] & 0xFFFFull)] : 0.0;
-        local += pv[e];
-    }
-    double incl = local;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const double o = shfl_up_f64(incl, d);
-        if (lane >= d) incl += o;
-    }
-    double before = incl - local;
+    tot = uniform_f64(group_sum<64>(tot));
     const double thresh = tau * tot;
+
+    // 3. the bracket
+    const auto bits = [](double v) { return static_cast<u64>(__double_as_longlong(v)); };
+    u64 lo = 0, hi = (bits(uniform_f64(rz)) | 0xFFFFull) + 1;   // (no probability exceeds exp(0) / z)
+    int n_lo = n, n_hi = 0;                                      // entries from lo, from hi on
+    double mass_hi = 0.0;                                        // mass from hi on
+    u64 mid = bits(uniform_f64((1.0 - tau) * tot * __builtin_amdgcn_rcp(static_cast<double>(n)) * 0.999));
+#pragma unroll 1
+    while (n_lo - n_hi > FEW && hi - lo > 1) {
+        if (mid <= lo || mid >= hi) mid = lo + (hi - lo) / 2;
+        double m = 0.0;
+        int c = 0;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {
+            const bool ge = key[e] >= mid;
+            m += ge ? p[e] : 0.0;
+            c += __popcll(__builtin_amdgcn_ballot_w64(ge));
+        }
+        m = uniform_f64(group_sum<64>(m));
+        if (m >= thresh) lo = mid, n_lo = c;
+        else hi = mid, n_hi = c, mass_hi = m;
+        mid = 0;
+    }
+    // 4. the entries in it, one per lane: kept iff the mass before them is below the threshold; the smallest kept key is
+    // the cut (an entry without mass is never kept)
+    int few = 0;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
-        if (pv[e] > 0.0 && before < thresh) flag[0xFFFF - static_cast<int>(key[e] & 0xFFFFull)] = 1;
-        before += pv[e];
-    }
-    __builtin_amdgcn_wave_barrier();   // the flags are read back by other lanes of this wave only
-
-    // 5. fix-block overrides and causal rules, then the row goes out
-    for (int j = lane; j < s.Tn; j += 64) {
-        uint8_t m = 0;
-        if (j < n) {
-            m = flag[j];
-            if (sk[j] < theta) m = 1;
-            if (causal && j == (i * BQ) / BK) m = 1;
+        const bool in = key[e] >= lo && key[e] < hi && key[e] != 0;
+        const u64 bal = __builtin_amdgcn_ballot_w64(in);
+        if (in) {
+            const int at = few + __popcll(bal & ((1ull << lane) - 1ull));
+            cand[2 * at] = __longlong_as_double(static_cast<long long>(key[e]));
+            cand[2 * at + 1] = p[e];
         }
-        out[j] = m;
+        few += __popcll(bal);
     }
+    __builtin_amdgcn_wave_barrier();   // (written and read by this wave only, whose LDS accesses complete in order)
+    const double my_key = cand[2 * min(lane, FEW - 1)], my_p = cand[2 * min(lane, FEW - 1) + 1];
+    double before = mass_hi;
+#pragma unroll 4
+    for (int c = 0; c < few; ++c) before += cand[2 * c] > my_key ? cand[2 * c + 1] : 0.0;
+    const bool kept = lane < few && my_p > 0.0 && before < thresh;
+    // (keys are positive as fp64 numbers and order alike)
+    const double cut = -uniform_f64(wave_max(kept ? -my_key : NEG));
+    const u64 from = cut < -NEG ? bits(cut) : hi;
+
+    // 5. fix-block overrides and causal rules
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        const int j = 64 * e + lane;
+        const bool m = (key[e] >= from && p[e] > 0.0) || (fix >> e & 1) || (causal && j == (i * BQ) / BK);
+        if (j < s.Tn) out[j] = j < n && m ? 1 : 0;
+    }
+    for (int j = 64 * EPL + lane; j < s.Tn; j += 64) out[j] = 0;
 }
-// The same with the fewest ranks per lane that hold the row: a causal row of a quarter (half) of the blocks sorts a
-// quarter (half) of the ranks in fewer stages.  Causal predictor call, with the logits tiles left out that no row sees:
+// The same with the fewest entries per lane that hold the row: a causal row of a quarter (half) of the blocks.  Causal predictor call, with the logits tiles left out that no row sees:
 // 428 against 471 us at 32 x 65536 x 128, 365 against 423 us at 8 x 131072 x 128 (TopCdf at 32 x 32768: 75 against 108 us).
 template <int EPL, class RowAt>
 __device__ __forceinline__ void topcdf_row_of(RowAt row_at, const int i, const double sim_q_i, const double* __restrict__ sk,
                                               const Shape& s, const double tau, const double theta, const int causal,
-                                              const int lane, double* pval, uint8_t* flag, uint8_t* __restrict__ out) {
+                                              const int lane, double* cand, uint8_t* __restrict__ out) {
     const int n = visible_blocks(s, i, causal);
     if constexpr (EPL >= 8) {
         if (n <= 16 * EPL) {
-            topcdf_row<EPL / 4>(row_at, i, sim_q_i, sk, s, tau, theta, causal, n, lane, pval, flag, out);
+            topcdf_row<EPL / 4>(row_at, i, sim_q_i, sk, s, tau, theta, causal, n, lane, cand, out);
             return;
         }
     }
     if constexpr (EPL >= 4) {
         if (n <= 32 * EPL) {
-            topcdf_row<EPL / 2>(row_at, i, sim_q_i, sk, s, tau, theta, causal, n, lane, pval, flag, out);
+            topcdf_row<EPL / 2>(row_at, i, sim_q_i, sk, s, tau, theta, causal, n, lane, cand, out);
             return;
         }
     }
-    topcdf_row<EPL>(row_at, i, sim_q_i, sk, s, tau, theta, causal, n, lane, pval, flag, out);
+    topcdf_row<EPL>(row_at, i, sim_q_i, sk, s, tau, theta, causal, n, lane, cand, out);
 }
 
 // One mask row per wave, the logits from memory.
@@ -512,9 +431,7 @@ __global__ __launch_bounds__(256) void topcdf_wave_kernel(const double* __restri
                                                            const double* __restrict__ sim_k, Shape s,
                                                            HeadParams tau_h, HeadParams theta_h, int causal,
                                                            int n_rows, uint8_t* __restrict__ mask) {
-    constexpr int NPAD = 64 * EPL;
-    __shared__ double pval[4][NPAD];
-    __shared__ uint8_t flag[4][NPAD];
+    __shared__ __align__(16) double cand[4][2 * FEW];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rowid = __builtin_amdgcn_readfirstlane(static_cast<int>(blockIdx.x) * 4 + wave);   // (b, h, i) flattened
     if (rowid >= n_rows) return;
@@ -525,7 +442,7 @@ __global__ __launch_bounds__(256) void topcdf_wave_kernel(const double* __restri
     const long long op_row = (long long)op * s.Tm + i;
     const double* row = logits + op_row * s.Tn;
     topcdf_row_of<EPL>([&](int j) { return row[j]; }, i, sim_q[op_row], sim_k + (long long)op * s.Tn, s, static_cast<double>(tau_h.v[h]),
-                    static_cast<double>(theta_h.v[h]), causal, lane, pval[wave], flag[wave],
+                    static_cast<double>(theta_h.v[h]), causal, lane, cand[wave],
                     mask + (long long)rowid * s.Tn);
 }
 
@@ -545,8 +462,7 @@ __global__ __launch_bounds__(64 * R) void predict_quant_kernel(
     constexpr int NPAD = 64 * EPL;
     static_assert(R % 4 == 0 && R <= 16, "rows of one 16-row tile, whole groups of 256 threads");
     struct Rows {
-        double lg[R][NPAD];       // logits, then probabilities
-        uint8_t flag[R][NPAD];
+        double lg[R][NPAD];       // logits, then a row's candidates
     };
     struct Quant {
         float mean[D];
@@ -583,7 +499,7 @@ __global__ __launch_bounds__(64 * R) void predict_quant_kernel(
         const double* row = lds.rows.lg[wave];
         topcdf_row_of<EPL>([&](int j) { return row[j]; }, i, sim_q[bh * s.Tm + i], sim_k + bh * s.Tn, s,
                         static_cast<double>(tau_h.v[h]), static_cast<double>(theta_h.v[h]), causal, lane,
-                        lds.rows.lg[wave], lds.rows.flag[wave], mask + (bh * s.Tm + i) * s.Tn);
+                        lds.rows.lg[wave], mask + (bh * s.Tm + i) * s.Tn);
         return;
     }
     id -= n_pred;
