@@ -252,10 +252,12 @@ int sparge_rel_l1(const void* O, const void* O_ref, const sparge_desc* desc, dou
  * sparsity, worst error}.  pv_dtype of desc selects the P~V product that is tuned.
  * This is the one entry point that synchronises: it reads error sums and counters back after every 5 (d = 64) or
  * 10 (d = 128) candidates, or after up to 16 that small searches run in one launch on all inputs, and it blocks until the
- * stream has finished.  Workspace: sparge_tune_workspace_bytes (256-byte aligned); a small search that gets less runs its
- * candidates one by one if that fits.  SPARGE_ENOSPACE also where the host has no memory for the tables.
+ * stream has finished.  Workspace (256-byte aligned): sparge_tune_workspace_bytes is enough; a small search that gets
+ * sparge_tune_workspace_batched_bytes (room for the outputs and masks of a launch's candidates, up to 50 MiB more)
+ * takes several candidates per launch.  SPARGE_ENOSPACE also where the host has no memory for the tables.
  */
 int sparge_tune_workspace_bytes(const sparge_desc* desc, int n_inputs, size_t* bytes /* host, out */);
+int sparge_tune_workspace_batched_bytes(const sparge_desc* desc, int n_inputs, size_t* bytes /* host, out */);
 int sparge_tune(const void* const* Q, const void* const* K, const void* const* V, int n_inputs,
                 const sparge_desc* desc, const float* tau_grid, int n_tau, const float* theta_grid, int n_theta,
                 const float* lambda_grid, int n_lambda, float l1, float l2, float sm_scale, int causal,

@@ -68,6 +68,7 @@ def load_library() -> ctypes.CDLL:
     f64p = ctypes.POINTER(ctypes.c_double)
     lib.sparge_rel_l1.argtypes = [vp, vp, dp, vp, vp]
     lib.sparge_tune_workspace_bytes.argtypes = [dp, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)]
+    lib.sparge_tune_workspace_batched_bytes.argtypes = [dp, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)]
     lib.sparge_tune.argtypes = [ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.POINTER(vp), ctypes.c_int, dp,
                                 f32p, ctypes.c_int, f32p, ctypes.c_int, f32p, ctypes.c_int,
                                 ctypes.c_float, ctypes.c_float, ctypes.c_float, ctypes.c_int,
@@ -82,7 +83,7 @@ def load_library() -> ctypes.CDLL:
                                    ctypes.c_size_t, vp]
     for name in ("sparge_workspace_bytes", "sparge_quantize", "sparge_predict", "sparge_attn_quantized",
                  "sparge_attn", "sparge_forward", "sparge_mask_to_lut", "sparge_item_order", "sparge_v_tiles", "sparge_attn_tiled", "sparge_v_tiles_bytes",
-                 "sparge_rel_l1", "sparge_tune_workspace_bytes", "sparge_tune", "sparge_hilbert_order",
+                 "sparge_rel_l1", "sparge_tune_workspace_bytes", "sparge_tune_workspace_batched_bytes", "sparge_tune", "sparge_hilbert_order",
                  "sparge_permute_tokens"):
         getattr(lib, name).restype = ctypes.c_int
     _LIB = lib
@@ -357,7 +358,7 @@ def sparge_tune(inputs, tau_grid, theta_grid, lambda_grid, l1: float, l2: float,
     d = _desc(Q0, pv_fp8)
     H, n = Q0.shape[1], len(inputs)
     need = ctypes.c_size_t(0)
-    _check(load_library().sparge_tune_workspace_bytes(ctypes.byref(d), n, ctypes.byref(need)))
+    _check(load_library().sparge_tune_workspace_batched_bytes(ctypes.byref(d), n, ctypes.byref(need)))
     ws = torch.empty(need.value, dtype=torch.uint8, device=Q0.device)
     arr = lambda k: (ctypes.c_void_p * n)(*[t[k].data_ptr() for t in inputs])
     fl = lambda xs: (ctypes.c_float * len(xs))(*[float(x) for x in xs])

@@ -632,7 +632,18 @@ int sparge_tune_workspace_bytes(const sparge_desc* desc, int n_inputs, size_t* b
     int rc = check_desc(desc, &s);
     if (rc) return rc;
     if (n_inputs < 1 || !bytes) return fail(SPARGE_EINVAL, "n_inputs must be >= 1 and bytes not NULL");
-    *bytes = std::max(tune_layout(s, n_inputs, false).total, tune_layout(s, n_inputs, true).total);
+    // a forward pass' workspace and the full-attention output per input, one output more (spans of the caller's strides)
+    const size_t span = (size_t)(s.B - 1) * s.sb + (size_t)(s.H - 1) * s.sh + (size_t)(s.N - 1) * s.sn + s.d;
+    const size_t out = align256(span * sizeof(uint16_t));
+    *bytes = (align256(plan(s, SPARGE_WS_FORWARD).total) + out) * n_inputs + out;
+    return SPARGE_OK;
+}
+
+int sparge_tune_workspace_batched_bytes(const sparge_desc* desc, int n_inputs, size_t* bytes) {
+    Shape s;
+    int rc = sparge_tune_workspace_bytes(desc, n_inputs, bytes);
+    if (rc || (rc = check_desc(desc, &s))) return rc;
+    *bytes = std::max(*bytes, tune_layout(s, n_inputs, false).total);
     return SPARGE_OK;
 }
 

@@ -152,18 +152,17 @@ def test_settings_of_one_launch_equal_settings_one_by_one(sp, B, H, N, d, causal
     grids = ([0.5, 0.7, 0.9], [-0.5, 0.2, 0.4, 0.6, 0.8, 0.9], [-10.0 + 0.5 * n for n in range(18)])   # 18 settings in each stage
     print(f"B={B} H={H} N={N} d={d} causal={causal} pv_fp8={pv_fp8}", flush=True)
     whole = sp.sparge_tune(inputs, *grids, 0.2, 0.25, causal=causal, pv_fp8=pv_fp8)
-    empty, ran = torch.empty, 0
-    for part in (0.9, 0.7, 0.5, 0.3):
-        monkeypatch.setattr(torch, "empty", lambda n, **k: empty(int(n * part), **k))
-        try:
-            got = sp.sparge_tune(inputs, *grids, 0.2, 0.25, causal=causal, pv_fp8=pv_fp8)
-        except sp.SpargeError as err:
-            assert "workspace" in str(err)
-            break
-        finally:
-            monkeypatch.undo()
-        ran += 1
-        assert np.array_equal(got["stage1"], whole["stage1"]) and np.array_equal(got["stage2"], whole["stage2"]), part
-        assert all(got[k] == whole[k] for k in ("tau", "theta", "lam", "sparsity", "l1")), part
-    assert ran > 0
+    import ctypes
+    from paper_2502_18137_amd import binding
+    desc, small, large = binding._desc(inputs[0][0], pv_fp8), ctypes.c_size_t(0), ctypes.c_size_t(0)
+    lib = sp.load_library()
+    assert lib.sparge_tune_workspace_bytes(ctypes.byref(desc), 3, ctypes.byref(small)) == 0
+    assert lib.sparge_tune_workspace_batched_bytes(ctypes.byref(desc), 3, ctypes.byref(large)) == 0
+    assert small.value < large.value
+    empty = torch.empty
+    monkeypatch.setattr(torch, "empty", lambda n, **k: empty(small.value, **k))
+    got = sp.sparge_tune(inputs, *grids, 0.2, 0.25, causal=causal, pv_fp8=pv_fp8)
+    monkeypatch.undo()
+    assert np.array_equal(got["stage1"], whole["stage1"]) and np.array_equal(got["stage2"], whole["stage2"])
+    assert all(got[k] == whole[k] for k in ("tau", "theta", "lam", "sparsity", "l1"))
     assert N < 300 or len(np.unique(whole["stage1"][..., 0, 0])) > 3      # (a single key block is always kept)
