@@ -20,7 +20,7 @@ namespace sparge {
 
 namespace {
 
-constexpr int SPLIT_WAVES = 4;   // softmax waves, and as many others: d / 32 product waves, the rest copies K_hat
+constexpr int SPLIT_WAVES = 4;   // softmax waves, and as many others: d / 32 product waves, the rest copies tiles
 
 struct SplitArgs {
     const void* Qp;
@@ -76,7 +76,8 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     const float NEG = -__builtin_inff();
     constexpr int KB = QK16 && D == 128 ? 1 : 2;   // K_hat buffers: rounds ahead (LDS holds no second one there)
     __shared__ __align__(1024) unsigned char Ks[KB][NW][K_DMA * 1024];
-    __shared__ __align__(1024) unsigned char Vs[NDT][NW][VT_DMA * 1024];   // a product wave's channels of the four tiles
+    constexpr int VB = D == 64 ? 2 : 1;            // V buffers
+    __shared__ __align__(1024) unsigned char Vs[VB][NDT][NW][VT_DMA * 1024];   // a product wave's channels of the four tiles
     __shared__ __align__(16) v4i ps[NW][NV][64];   // P~ of the round's tiles as the P~V operand
     __shared__ __align__(16) float row_max[RG][NW];
     __shared__ float tile_sum[NW][64];
@@ -84,6 +85,9 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     __shared__ __align__(8) uint16_t jl[SPLIT_MAX_TN + 4 * NW];   // kept key blocks of this row, ascending; then zeros
 
     const Shape& s = a.s;
+    // the arguments in one round trip (left to themselves the loads of an argument wait for its first use, one after the other)
+    asm volatile("" ::"s"(a.Qp), "s"(a.Kp), "s"(a.q_scale), "s"(a.k_scale), "s"(a.v_tiles), "s"(a.mask), "s"(a.stats), "s"(a.per_xcd),
+                 "s"(a.sm_scale), "s"(s.H), "s"(s.N), "s"(s.Tm), "s"(s.Tn), "s"(s.op_bh), "s"(s.dense_bh), "s"(s.by_setting), "s"(s.one_mask));
     const int n_rg = (s.N + RG - 1) / RG;
     // consecutive workgroups land on different XCDs: each XCD takes a contiguous range of row groups, so that its L2
     // serves few heads; causal heads start with their longest rows
@@ -98,6 +102,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     const int qrow = g * RG + l32;
     const bool row_counts = qrow < s.N;
 
+    const float lam2 = a.lambda_h.v[s.param(own, h)] * LOG2E;
     v4i qf[NSTEP];
 #pragma unroll
     for (int st = 0; st < NSTEP; ++st) {
@@ -114,19 +119,20 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     const int jvis = CAUSAL ? min(jmax, (g * RG + RG - 1) / BK + 1) : jmax;
     int listed = 0, cnt = 0;   // kept blocks of the Q block; those that this group sees
     {
-        unsigned int mk[NW] = {1, 1, 1, 1};
         static_assert(SPLIT_MAX_TN == 64 * NW, "one flag per lane and wave");
-        if (a.mask && own >= 0) {   // (loads without conditions: all in flight together)
-            const uint8_t* mrow = a.mask + ((long long)(s.one_mask ? op : own) * s.Tm + i) * s.Tn;
+        // (loads without conditions and in one block, all in flight together; without a mask they read what they like)
+        const bool dense = !a.mask || own < 0;
+        const uint8_t* mrow = dense ? a.v_tiles : a.mask + ((long long)(s.one_mask ? op : own) * s.Tm + i) * s.Tn;
+        unsigned int mk[NW];
 #pragma unroll
-            for (int q = 0; q < NW; ++q) mk[q] = mrow[min(q * 64 + lane, jmax - 1)];
-        }
+        for (int q = 0; q < NW; ++q) mk[q] = mrow[min(q * 64 + lane, jmax - 1)];
         const float sc = QK16 ? 1.f : a.k_scale[(long long)op * s.Tn + min((wave & (NW - 1)) * 64 + lane, jmax - 1)];
         const float qs = (QK16 ? 1.f : a.q_scale[(long long)op * s.Tm + i]) * a.sm_scale * LOG2E;
+        asm volatile("" ::"v"(mk[0]), "v"(mk[1]), "v"(mk[2]), "v"(mk[3]), "v"(sc), "v"(qs), "v"(lam2));
 #pragma unroll
         for (int q = 0; q < NW; ++q) {
             const int j = q * 64 + lane;
-            const bool keep = mk[q] != 0 && j < jmax;
+            const bool keep = (dense || mk[q] != 0) && j < jmax;
             const unsigned long long bal = __builtin_amdgcn_ballot_w64(keep);
             if (q == wave && keep) {
                 const int pos = listed + __popcll(bal & ((1ull << lane) - 1ull));
@@ -140,7 +146,6 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     if (wave == NW && lane < 4 * NW) jl[listed + lane] = 0;   // copies behind the list fetch a tile nobody reads
     lds_barrier();
 
-    const float lam2 = a.lambda_h.v[s.param(own, h)] * LOG2E;
     float m_true = NEG, m_ref = NEG;
     // what both kinds of waves follow: the running maximum through the round's tiles (ml: their row maxima) ...
     float ml[NW], m[NW];
@@ -272,7 +277,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
         return;
     }
 
-    // ---- copies of K_hat: by two waves of their own, two tiles of a round each, or (d = 128) by the four product waves
+    // ---- copies: d = 64: by two waves of their own, two tiles of a round each; d = 128: by the four product waves
     const int hw = wave - NW;
     constexpr int K_TILES = D == 128 ? 1 : 2;
     const int k_tile0 = D == 128 ? hw : 2 * (hw - NDT);
@@ -303,39 +308,60 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
             }
         }
     };
-    if (D == 64 && hw >= NDT) {
-        if (cnt == 0) return;
-        copy_k(0, 0);
-        if (NW < cnt) {
-            copy_k(NW, 1);
-            dma_wait<K_TILES * K_DMA>();
-        } else {
-            dma_wait<0>();
-        }
-        lds_barrier();
-        int buf = 0;
-        for (int t0 = 0; t0 < cnt; t0 += NW, buf ^= 1) {
-            lds_barrier();   // A: the round's scores are made, its K_hat is free
-            if (t0 + 2 * NW < cnt) {
-                copy_k(t0 + 2 * NW, buf);
-                dma_wait<K_TILES * K_DMA>();   // K_hat of the next round has landed
-            } else {
-                dma_wait<0>();
-            }
-            lds_barrier();   // B
-        }
-        return;
-    }
-
-    // ---- product waves
-    const unsigned char* vbase = a.v_tiles + (long long)op * s.Tn * V_BYTES + hw * (VT_DMA * 1024);
-    const uint32_t v_lds = lds_address(Vs[hw][0]);
+    // ---- copies of V, by the tile's 32-channel parts: d = 64: the copying waves again, both parts of two tiles each; d = 128:
+    // a product wave its own part of all four
     uint32_t v_src[VT_DMA];
 #pragma unroll
     for (int n = 0; n < VT_DMA; ++n) {
         const int row = n * 8 + lane / 8;
         v_src[n] = FP8 ? n * 1024 + lane * 16 : row * 128 + (((lane % 8) ^ swz<128>(row)) * 16);
     }
+    const unsigned char* vbase = a.v_tiles + (long long)op * s.Tn * V_BYTES;
+    if (D == 64 && hw >= NDT) {
+        auto copy_v = [&](int t0, int buf) {
+#pragma unroll
+            for (int k = 0; k < K_TILES; ++k) {
+                const int j = __builtin_amdgcn_readfirstlane(static_cast<int>(jl[t0 + k_tile0 + k]));
+#pragma unroll
+                for (int dt = 0; dt < NDT; ++dt) {
+                    const uint32_t dst = lds_address(Vs[0][dt][k_tile0 + k]) + buf * (NDT * NW * VT_DMA * 1024);
+#pragma unroll
+                    for (int n = 0; n < VT_DMA; ++n)
+                        dma16_at(vbase + (long long)j * V_BYTES + dt * (VT_DMA * 1024), v_src[n], dst, n * 1024);
+                }
+            }
+        };
+        constexpr int KC = K_TILES * K_DMA, VC = K_TILES * NDT * VT_DMA;   // copies of a wave per round
+        if (cnt == 0) return;
+        copy_k(0, 0);
+        copy_v(0, 0);
+        if (NW < cnt) {
+            copy_k(NW, 1);
+            copy_v(NW, 1);
+            dma_wait<KC + 2 * VC>();   // K_hat of the first round has landed
+        } else {
+            dma_wait<VC>();
+        }
+        lds_barrier();
+        int buf = 0;
+        // in flight at the top of a round, oldest first: its V, K_hat and V of the next round
+        for (int t0 = 0; t0 < cnt; t0 += NW, buf ^= 1) {
+            const bool next = t0 + NW < cnt, more = t0 + 2 * NW < cnt;
+            if (next) dma_wait<KC + VC>();   // this round's V
+            else dma_wait<0>();
+            lds_barrier();   // A: the round's scores are made, its K_hat is free
+            if (more) copy_k(t0 + 2 * NW, buf);
+            if (more) dma_wait<VC + KC>();   // K_hat of the next round
+            else if (next) dma_wait<VC>();
+            lds_barrier();   // B: the round's V is in registers
+            if (more) copy_v(t0 + 2 * NW, buf);
+        }
+        return;
+    }
+
+    // ---- product waves
+    const uint32_t v_lds = lds_address(Vs[0][hw][0]);
+    vbase += hw * (VT_DMA * 1024);
     int vj[NW];   // key blocks of the V tiles that are copied next
     auto list_v = [&](int t0) {
         const uint2 four = *reinterpret_cast<const uint2*>(&jl[t0]);
@@ -349,14 +375,15 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     float l = 0.f;
     int pv_done = 0;
     if (cnt > 0) {
-        if (D == 128) copy_k(0, 0);
-        if (D == 128 && KB == 2 && NW < cnt) copy_k(NW, 1);
-        list_v(0);
+        if constexpr (D == 128) {
+            copy_k(0, 0);
+            list_v(0);
 #pragma unroll
-        for (int w = 0; w < NW; ++w)
+            for (int w = 0; w < NW; ++w)
 #pragma unroll
-            for (int n = 0; n < VT_DMA; ++n) copy_v(w, n);
-        if (D == 128) {   // K_hat of the first round has landed
+                for (int n = 0; n < VT_DMA; ++n) copy_v(w, n);
+            if (KB == 2 && NW < cnt) copy_k(NW, 1);
+            // K_hat of the first round has landed
             if (KB == 2 && NW < cnt) dma_wait<K_DMA + NW * VT_DMA>();
             else dma_wait<NW * VT_DMA>();
         }
@@ -365,8 +392,10 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     int buf = 0;
     for (int t0 = 0; t0 < cnt; t0 += NW) {
         const bool more = t0 + NW < cnt;
-        list_v(t0 + NW);
-        dma_wait<0>();   // this round's V; K_hat of the next one
+        if constexpr (D == 128) {
+            list_v(t0 + NW);
+            dma_wait<0>();   // this round's V; K_hat of the next one
+        }
         lds_barrier();   // A
         const bool any_move = follow(t0);
         v4i vf[NW][NV];
@@ -374,7 +403,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
         for (int w = 0; w < NW; ++w)
 #pragma unroll
             for (int p = 0; p < NV; ++p)
-                vf[w][p] = *reinterpret_cast<const v4i*>(&Vs[hw][w][0] + (FP8 ? p * 1024 + lane * 16 : l32 * 128 + (((p * 2 + hl) ^ swz<128>(l32)) * 16)));
+                vf[w][p] = *reinterpret_cast<const v4i*>(&Vs[VB == 2 ? buf : 0][hw][w][0] + (FP8 ? p * 1024 + lane * 16 : l32 * 128 + (((p * 2 + hl) ^ swz<128>(l32)) * 16)));
         // stage-2 decisions (Alg. 1 line 15); a tile that is not there has -inf and is not executed
         int votes = 0;
 #pragma unroll
@@ -388,7 +417,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
         }
         pv_done += __builtin_popcount(votes);
         // V of the next round takes the place of this one's, half of it here and half beside the products
-        if (more) {
+        if (D == 128 && more) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
             for (int w = 0; w < NW / 2; ++w)
@@ -398,8 +427,8 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
         if (D == 128) {
             if (t0 + KB * NW < cnt) copy_k(t0 + KB * NW, buf);
             if (KB == 1) dma_wait<0>();
-            else buf ^= 1;
         }
+        buf ^= KB == 2;
         lds_barrier();   // B
         // ---- l and O of the own channels, tile by tile
         v4i pf[NW][NV];
@@ -420,16 +449,18 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
                 for (int p = 0; p < NV; ++p) O = mfma16<DT>(vf[w][p], pf[w][p], O);
             }
         };
-        if (votes == 15 && !moved && more) {   // the usual round, without branches
+        const bool copies = D == 128 && more;
+        if (votes == 15 && !moved && (D == 64 || more)) {   // the usual round, without branches
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
                 l += ts[w];
                 pv(w);
+                if constexpr (D == 128)
 #pragma unroll
-                for (int n = 0; n < VT_DMA / 2; ++n) copy_v(NW / 2 + w / 2, (w & 1) * (VT_DMA / 2) + n);
+                    for (int n = 0; n < VT_DMA / 2; ++n) copy_v(NW / 2 + w / 2, (w & 1) * (VT_DMA / 2) + n);
             }
         } else {
-            if (more) {
+            if (copies) {
 #pragma unroll
                 for (int w = NW / 2; w < NW; ++w)
 #pragma unroll

@@ -35,6 +35,13 @@ __device__ __forceinline__ int visible_blocks(const Shape& s, int i, int causal)
     return causal ? min(s.Tn, 2 * i + 2) : s.Tn;
 }
 
+// The logit of a key block from its sum over keys; `keys`: keys from the block's first one on.  (A full block's division by
+// 64 is a multiplication, exactly; an fp64 division costs as much time on the vector ALU as half a matrix instruction
+// on its pipe, and a wave of the logits has one per logit: LOGIT_TIMES.)
+__device__ __forceinline__ double mean_logit(double sum, int keys, double sm_scale) {
+    return sm_scale * (keys >= BK ? sum * (1.0 / BK) : sum / static_cast<double>(keys));
+}
+
 // Compressed logits as an fp64 matrix product on the matrix cores: a wave computes RT x 16 pooled query rows x 64
 // key blocks with v_mfma_f64_16x16x4_f64 (operands: lane = row or column + 16 * k; result register r of a
 // lane = row 4 r + lane / 16, column lane % 16).  The pooled queries are row-major, the key sums
@@ -80,13 +87,12 @@ __global__ __launch_bounds__(256) void logits_kernel(const double* __restrict__ 
     for (int t = 0; t < 4; ++t) {
         const int j = j0 + 16 * t + l16;
         if (j >= s.Tn) continue;
-        const double cnt = static_cast<double>(min(BK, s.N - j * BK));
 #pragma unroll
         for (int u = 0; u < RT; ++u)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int i = i0 + 16 * u + 4 * r + kk;
-                if (i < s.Tm) logits[(bh * s.Tm + i) * s.Tn + j] = sm_scale * (acc[u][t][r] / cnt);
+                if (i < s.Tm) logits[(bh * s.Tm + i) * s.Tn + j] = mean_logit(acc[u][t][r], s.N - j * BK, sm_scale);
             }
     }
 }
@@ -488,9 +494,8 @@ __global__ __launch_bounds__(64 * R) void predict_quant_kernel(
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qrow[c], kcol[(long long)c * s.Tn], acc, 0, 0, 0);
             const int j = j0 + l16;
             if (j < s.Tn) {
-                const double cnt = static_cast<double>(min(BK, s.N - j * BK));
 #pragma unroll
-                for (int r = 0; r < R / 4; ++r) lds.rows.lg[4 * r + kk][j] = sm_scale * (acc[r] / cnt);
+                for (int r = 0; r < R / 4; ++r) lds.rows.lg[4 * r + kk][j] = mean_logit(acc[r], s.N - j * BK, sm_scale);
             }
         }
         __syncthreads();
