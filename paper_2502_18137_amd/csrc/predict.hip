@@ -515,14 +515,16 @@ __global__ __launch_bounds__(64 * R) void predict_quant_kernel(
     // and l + 48 of k_mean_kernel hold, combined as there
     for (int c = threadIdx.x >> 4; c < D; c += 4 * R) {
         const double* row = ksum_t + (bh * D + c) * s.Tn;
-        double a[4] = {0.0, 0.0, 0.0, 0.0};
+        double v[EPL][4], a[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int e = 0; e < EPL; ++e)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int j = 64 * e + 16 * q + (lane & 15);
-                if (j < s.Tn) a[q] += row[j];
-            }
+            for (int q = 0; q < 4; ++q)   // (loads without conditions, all in flight: one by one they were a memory latency each)
+                v[e][q] = row[min(64 * e + 16 * q + (lane & 15), s.Tn - 1)];
+#pragma unroll
+        for (int e = 0; e < EPL; ++e)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a[q] += 64 * e + 16 * q + (lane & 15) < s.Tn ? v[e][q] : 0.0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) a[q] = group_sum<16>(a[q]);
         const double sum = (a[0] + a[1]) + (a[2] + a[3]);

@@ -249,12 +249,17 @@ __device__ __forceinline__ void v_tile(VTileLds<D>& tile, const uint16_t* __rest
     constexpr int PITCH = VTileLds<D>::PITCH;
     uint16_t* const lds = tile.v;
     constexpr int CPR = D / 8;  // 16-byte chunks per key row
-    for (int idx = threadIdx.x; idx < BK * CPR; idx += 256) {
-        const int row = idx / CPR, col = idx % CPR;
-        const int key = j * BK + row;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (key < s.N) v = *reinterpret_cast<const uint4*>(base + (long long)key * s.sn + col * 8);
-        *reinterpret_cast<uint4*>(&lds[row * PITCH + col * 8]) = v;
+    constexpr int NL = BK * CPR / 256;
+    uint4 v[NL];
+#pragma unroll
+    for (int n = 0; n < NL; ++n) {   // (loads without conditions, all in flight before the first goes to LDS)
+        const int idx = threadIdx.x + n * 256, row = idx / CPR, col = idx % CPR;
+        v[n] = *reinterpret_cast<const uint4*>(base + (long long)min(j * BK + row, s.N - 1) * s.sn + col * 8);
+    }
+#pragma unroll
+    for (int n = 0; n < NL; ++n) {
+        const int idx = threadIdx.x + n * 256, row = idx / CPR, col = idx % CPR;
+        *reinterpret_cast<uint4*>(&lds[row * PITCH + col * 8]) = j * BK + row < s.N ? v[n] : make_uint4(0u, 0u, 0u, 0u);
     }
     __syncthreads();
     uint16_t* out = tiles + (bh * s.Tn + j) * (long long)(D * BK);
