@@ -35,19 +35,13 @@ __device__ __forceinline__ int visible_blocks(const Shape& s, int i, int causal)
     return causal ? min(s.Tn, 2 * i + 2) : s.Tn;
 }
 
-// The logit of a key block from its sum over keys; `keys`: keys from the block's first one on.  (A full block's division by
-// 64 is a multiplication, exactly; an fp64 division costs as much time on the vector ALU as half a matrix instruction
-// on its pipe, and a wave of the logits has one per logit: LOGIT_TIMES.)
-__device__ __forceinline__ double mean_logit(double sum, int keys, double sm_scale) {
-    return sm_scale * (keys >= BK ? sum * (1.0 / BK) : sum / static_cast<double>(keys));
-}
-
 // Compressed logits as an fp64 matrix product on the matrix cores: a wave computes RT x 16 pooled query rows x 64
 // key blocks with v_mfma_f64_16x16x4_f64 (operands: lane = row or column + 16 * k; result register r of a
 // lane = row 4 r + lane / 16, column lane % 16).  The pooled queries are row-major, the key sums
 // transposed ([d][Tn]), so the B operand loads are lane-coalesced; both operands stay L2-resident and go
 // straight from the caches into the operands, RT + 4 loads for 4 RT matrix instructions per step of 4 channels
-// (RT is chosen at launch).
+// (RT is chosen at launch).  What bounds it is the matrix instruction itself: one per 100-115 cycles and SIMD however many
+// waves offer it (counters: waves wait for issue 86 % of the time, for memory 7 %), half the nominal rate.
 typedef double v4d __attribute__((ext_vector_type(4)));
 template <int D, int RT>
 __global__ __launch_bounds__(256) void logits_kernel(const double* __restrict__ pooled_q,
@@ -87,12 +81,13 @@ __global__ __launch_bounds__(256) void logits_kernel(const double* __restrict__ 
     for (int t = 0; t < 4; ++t) {
         const int j = j0 + 16 * t + l16;
         if (j >= s.Tn) continue;
+        const double cnt = static_cast<double>(min(BK, s.N - j * BK));
 #pragma unroll
         for (int u = 0; u < RT; ++u)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int i = i0 + 16 * u + 4 * r + kk;
-                if (i < s.Tm) logits[(bh * s.Tm + i) * s.Tn + j] = mean_logit(acc[u][t][r], s.N - j * BK, sm_scale);
+                if (i < s.Tm) logits[(bh * s.Tm + i) * s.Tn + j] = sm_scale * (acc[u][t][r] / cnt);
             }
     }
 }
@@ -456,9 +451,11 @@ __global__ __launch_bounds__(256) void topcdf_wave_kernel(const double* __restri
 // statistics: the first n_pred workgroups take R mask rows each (the logits of the 16 x 16 tiles over these rows
 // by R waves into LDS, then one row per wave), the others quantize `per_wg` K blocks of one head, with the head's
 // token mean of K computed on the spot (in the order k_mean_kernel adds: the same bits).
-// What bounds it is latency: the logits' operand loads, one chain of d / 4 fp64 matrix products, the softmax's
-// reductions and the sort's stages, one after the other; logits through memory and a launch for each of the
-// four passes came on top of that.
+// What bounds it is latency: the logits' operand loads, one chain of d / 4 fp64 matrix products (140 cycles each while
+// one wave has the unit), the softmax's reductions and the probes for the cut, one after the other; logits through
+// memory and a launch for each of the four passes came on top of that.  (The logits as fp64 fused multiply-adds, a wave
+// per d / 8 channels with the queries in scalar registers: 25.5 against 22.4 us a call at 2 x 2048 x 64, the scalar
+// loads wait for each other.)
 template <int D, int DT, int EPL, int R>
 __global__ __launch_bounds__(64 * R) void predict_quant_kernel(
     const double* __restrict__ pooled_q, const double* __restrict__ ksum_t, const double* __restrict__ sim_q,
@@ -494,8 +491,9 @@ __global__ __launch_bounds__(64 * R) void predict_quant_kernel(
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(qrow[c], kcol[(long long)c * s.Tn], acc, 0, 0, 0);
             const int j = j0 + l16;
             if (j < s.Tn) {
+                const double cnt = static_cast<double>(min(BK, s.N - j * BK));
 #pragma unroll
-                for (int r = 0; r < R / 4; ++r) lds.rows.lg[4 * r + kk][j] = mean_logit(acc[r], s.N - j * BK, sm_scale);
+                for (int r = 0; r < R / 4; ++r) lds.rows.lg[4 * r + kk][j] = sm_scale * (acc[r] / cnt);
             }
         }
         __syncthreads();
