@@ -31,7 +31,7 @@ PEAK_HBM = 8.0e12    # B/s
 # HBM-side bytes per launch of the attention kernel come from profiles/attn_kernel_hbm_traffic.txt (rocprofv3
 # --pmc FETCH_SIZE / WRITE_SIZE runs of this script scaled by a 1 GiB copy).  That file records the SHA-256 of
 # the kernel sources it was measured with; if the sources in the tree differ, `traffic` is null.
-KERNEL_SOURCES = ("attn.hip", "gen_attn_loop.py", "common.hpp")
+KERNEL_SOURCES = ("attn.hip", "attn_ops.hpp", "gen_attn_loop.py", "common.hpp")
 
 
 def kernel_sources_sha256() -> str:

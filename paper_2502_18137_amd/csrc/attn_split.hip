@@ -5,12 +5,18 @@
 // at 0.55 (d = 64) or 0.69 us (d = 128) a tile however empty the chip is.  Here a round takes tiles 4r .. 4r + 3 of the
 // group's list; four waves make their scores and P~, four more (d = 64: two) multiply with V:
 //   softmax wave w                                             product wave (32 channels)
-//   scores of tile 4r + w and their row maxima                 O += P~ V of round r - 1, tile by tile; V of round r on its way
+//   scores of tile 4r + w and their row maxima                 O += P~ V of round r - 1, tile by tile
 //   ---- barrier A: the row maxima of the four tiles are exchanged
 //   running maximum and moves of the reference maximum         the same, and the stage-2 decisions;
-//   through the four tiles in order; P~ of its tile against    V of round r into registers, V of round r + 1 on its way
+//   through the four tiles in order; P~ of its tile against    V of round r into registers
 //   the reference its place in the order gives
 //   ---- barrier B: P~ and its row sums are exchanged
+// K_hat and V are copied to LDS a round or two ahead, at d = 64 by two waves that do nothing else; LDS has no room for that
+// at d = 128, where the product waves copy beside their products.  A round takes 1.06 us at d = 64 and 1.73 us at d = 128
+// (2.2 and 2.8 us for its tiles one after the other in attn.hip), bound by the softmax waves' instructions (2200 of 2500
+// cycles) and, at d = 128, by the copies' 96 KB through the unit's 64 bytes a cycle.  On the way: operands loaded from
+// memory straight into registers, 2.0 / 3.5 us (32 rows of 32 bytes a load); one kind of wave for everything, 1.5 / 2.4
+// us; V copied between the products at d = 64 too, 1.22 us.
 // Everything that is decided or rounded per tile is decided and rounded as in attn.hip, and every sum has its order (P~ V:
 // tiles in list order on the same matrix instruction; l: a tile's own sum, then the sum of tiles), so the two kernels
 // give the same bits and the choice between them is one of speed alone (attn_split_pays).
