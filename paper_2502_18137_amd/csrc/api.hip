@@ -546,7 +546,7 @@ int sparge_forward(const void* Q, const void* K, const void* V, const sparge_des
     if ((e = hipStreamWaitEvent(side->stream, side->fork, 0)) != hipSuccess) return hip_fail(e, "wait fork");
     // from here on the second stream is joined whatever happens, so that a capture of the caller's stream can end
     int rc_side = SPARGE_OK;
-    // V tiles first: they need LDS, which the logits kernel beside them leaves free and TopCdf does not
+    // V tiles first: they need LDS, which the logits kernel beside them leaves free
     if ((e = retile_v(V, s, at<char>(ws, w.v_tiles), side->stream)) != hipSuccess) rc_side = hip_fail(e, "v_tiles");
     if (q8 && !rc_side) {
         if ((e = launch_k_mean(at<double>(ws, w.ksum_t), s, at<float>(ws, w.k_mean), side->stream)) != hipSuccess)
