@@ -10,15 +10,16 @@
 //   running maximum and moves of the reference maximum         the same, and the stage-2 decisions;
 //   through the four tiles in order; P~ of its tile against    V of round r into registers
 //   the reference its place in the order gives
-//   ---- barrier B: P~ and its row sums are exchanged
+//   ---- barrier B: P~ is exchanged; the row sums go from softmax wave to softmax wave
 // K_hat and V are copied to LDS a round or two ahead, at d = 64 by two waves that do nothing else; LDS has no room for that
-// at d = 128, where the product waves copy beside their products.  A round takes 1.06 us at d = 64 and 1.73 us at d = 128
-// (2.2 and 2.8 us for its tiles one after the other in attn.hip), bound by the softmax waves' instructions (2200 of 2500
-// cycles) and, at d = 128, by the copies' 96 KB through the unit's 64 bytes a cycle.  On the way: operands loaded from
+// at d = 128, where the product waves copy beside their products.  A round takes 1.10 us at d = 64 and 1.72 us at d = 128
+// (2.3 and 3.0 us for its tiles one after the other in attn.hip; FP8 P~V 1.04 and 1.35, 16-bit Q K^T 1.21 and 2.78 us), bound
+// by the softmax waves' instructions (2200 of 2600 cycles) and, at d = 128, by the copies' 96 KB through the unit's 64 bytes a
+// cycle.  (With a sum per tile for l, added up by the product waves, 1.02 and 1.91 us, but l in another order.)  On the way: operands loaded from
 // memory straight into registers, 2.0 / 3.5 us (32 rows of 32 bytes a load); one kind of wave for everything, 1.5 / 2.4
 // us; V copied between the products at d = 64 too, 1.22 us.
 // Everything that is decided or rounded per tile is decided and rounded as in attn.hip, and every sum has its order (P~ V:
-// tiles in list order on the same matrix instruction; l: a tile's own sum, then the sum of tiles), so the two kernels
+// tiles in list order on the same matrix instruction; l: one P~ after the other through all tiles), so the two kernels
 // give the same bits and the choice between them is one of speed alone (attn_split_pays).
 #include "attn_ops.hpp"
 
@@ -86,7 +87,9 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     __shared__ __align__(1024) unsigned char Vs[VB][NDT][NW][VT_DMA * 1024];   // a product wave's channels of the four tiles
     __shared__ __align__(16) v4i ps[NW][NV][64];   // P~ of the round's tiles as the P~V operand
     __shared__ __align__(16) float row_max[RG][NW];
-    __shared__ float tile_sum[NW][64];
+    __shared__ __align__(8) unsigned long long row_sums[64];   // per lane of the scores: l so far, tiles in it
+    volatile __attribute__((address_space(3))) unsigned long long* const row_sum =
+        (volatile __attribute__((address_space(3))) unsigned long long*)row_sums + (threadIdx.x & 63);
     __shared__ float scl[SPLIT_MAX_TN + 4 * NW];   // per kept tile: q_scale * k_scale * sm_scale * log2(e)
     __shared__ __align__(8) uint16_t jl[SPLIT_MAX_TN + 4 * NW];   // kept key blocks of this row, ascending; then zeros
 
@@ -150,6 +153,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
         }
     }
     if (wave == NW && lane < 4 * NW) jl[listed + lane] = 0;   // copies behind the list fetch a tile nobody reads
+    if (wave == NW) *row_sum = 0ull;
     lds_barrier();
 
     float m_true = NEG, m_ref = NEG;
@@ -181,6 +185,22 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
         int buf = 0;
         int j = jl[wave];
         float sc = scl[wave];
+        // l takes one P~ after the other, tile by tile: it goes from wave to wave, and a wave waits until it holds the tiles
+        // before its own.  Wave 0 adds its tile at the end of the round; waves 1, 2 and 3 add theirs in the next round, beside
+        // the scores, before barrier A and behind it: each after the one it waits for, which in that interval between two
+        // barriers waits for nobody itself, so every wait ends and is nearly always over before it begins.
+        float p[32];
+        float f_own = 1.f;   // the move of the reference maximum at the own tile
+        auto add_tile = [&](int t) {
+#pragma clang fp contract(off)   // (the move and the first addition round one after the other)
+            unsigned long long sum_n;
+            do sum_n = *row_sum;
+            while (__builtin_amdgcn_ballot_w64(static_cast<int>(sum_n >> 32) != t) != 0);
+            float l = __uint_as_float(static_cast<uint32_t>(sum_n)) * f_own;
+#pragma unroll
+            for (int e = 0; e < 32; ++e) l += p[e];
+            *row_sum = static_cast<unsigned long long>(static_cast<uint32_t>(t + 1)) << 32 | __float_as_uint(l);
+        };
         if (cnt > 0) lds_barrier();   // K_hat of the first round is there
         for (int t0 = 0; t0 < cnt; t0 += NW) {
             const bool live = t0 + wave < cnt;   // there is a tile for this wave
@@ -200,6 +220,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
                         else S[kh] = __builtin_amdgcn_mfma_i32_32x32x32_i8(kf, qf[st], c, 0, 0, 0);
                     }
                 }
+                if (wave == 1 && t0 > 0) add_tile(t0 - NW + 1);   // (the scores are not there yet)
                 // biased integers compare like the scores (-inf is a negative integer)
                 const int ju = __builtin_amdgcn_readfirstlane(j);
                 if (ju * BK + BK > s.N || (CAUSAL && ju * BK + BK - 1 > g * RG)) {
@@ -229,29 +250,32 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
                 }
                 m_loc = max_across_halves(m_loc);
             }
+            if (!live && wave == 1 && t0 > 0) add_tile(t0 - NW + 1);
             if (hl == 0) row_max[l32][wave] = m_loc;
+            if (wave == 2 && t0 > 0) add_tile(t0 - NW + 2);
             lds_barrier();   // A
+            if (wave == 3 && t0 > 0) add_tile(t0 - NW + 3);
             const bool any_move = follow(t0);
             float ref_own = m_ref;
+            f_own = 1.f;
             if (any_move) {
 #pragma unroll
                 for (int w = 0; w < NW; ++w) {
                     float f;
-                    moves(w, f);
-                    if (w == wave) ref_own = m_ref;
+                    const bool moved = moves(w, f);
+                    if (w == wave) {
+                        ref_own = m_ref;
+                        if (moved) f_own = f;
+                    }
                 }
             }
             if (live) {
                 float cx = __builtin_fmaf(-BIAS, sc, -ref_own);
                 if constexpr (FP8) cx += 6.807354927062988f;   // P~ scaled by 448 / 2^2: log2(448) - 2
                 if (ref_own == NEG) cx = 0.f;                  // a row that has seen no key yet: its scores are all -inf
-                float p[32];
 #pragma unroll
                 for (int e = 0; e < 32; ++e)
                     p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(__int_as_float(S[e >> 4][e & 15]), sc, cx));
-                float sum = p[0];
-#pragma unroll
-                for (int e = 1; e < 32; ++e) sum += p[e];
                 int pk[NV * 4];
                 if constexpr (FP8) {
 #pragma unroll
@@ -265,12 +289,17 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
                 }
 #pragma unroll
                 for (int q = 0; q < NV; ++q) ps[wave][q][lane] = v4i{pk[4 * q], pk[4 * q + 1], pk[4 * q + 2], pk[4 * q + 3]};
-                tile_sum[wave][lane] = sum;
+                if (wave == 0) add_tile(t0);
             }
             lds_barrier();   // B
             j = j_next;
             sc = sc_next;
             if (KB == 2) buf ^= 1;
+        }
+        if (cnt > 0) {
+            const int t = (cnt - 1) / NW * NW + wave;
+            if (wave > 0 && t < cnt) add_tile(t);
+            lds_barrier();   // l is there
         }
         if (a.stats && own >= 0 && threadIdx.x == 0) {   // row groups whose last row sees the key block; tiles once per Q block
             unsigned long long* st = a.stats + own * 4;
@@ -362,6 +391,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
             lds_barrier();   // B: the round's V is in registers
             if (more) copy_v(t0 + 2 * NW, buf);
         }
+        lds_barrier();
         return;
     }
 
@@ -378,7 +408,6 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     v16f O;
 #pragma unroll
     for (int r = 0; r < 16; ++r) O[r] = 0.f;
-    float l = 0.f;
     int pv_done = 0;
     if (cnt > 0) {
         if constexpr (D == 128) {
@@ -436,15 +465,12 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
         }
         buf ^= KB == 2;
         lds_barrier();   // B
-        // ---- l and O of the own channels, tile by tile
+        // ---- O of the own channels, tile by tile
         v4i pf[NW][NV];
-        float ts[NW];
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            ts[w] = tile_sum[w][lane];
+        for (int w = 0; w < NW; ++w)
 #pragma unroll
             for (int p = 0; p < NV; ++p) pf[w][p] = ps[w][p][lane];
-        }
         auto pv = [&](int w) {
             if constexpr (FP8) {
                 O = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
@@ -459,7 +485,6 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
         if (votes == 15 && !moved && (D == 64 || more)) {   // the usual round, without branches
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
-                l += ts[w];
                 pv(w);
                 if constexpr (D == 128)
 #pragma unroll
@@ -476,16 +501,16 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
             for (int w = 0; w < NW; ++w) {
                 if (t0 + w >= cnt) break;
                 if (moved >> w & 1) {
-                    l *= f[w];
 #pragma unroll
                     for (int r = 0; r < 16; ++r) O[r] *= f[w];
                 }
-                l += ts[w];
                 if (votes >> w & 1) pv(w);
             }
         }
     }
 
+    if (cnt > 0) lds_barrier();   // l is there
+    const float l = __uint_as_float(static_cast<uint32_t>(*row_sum));
     // ---- O_i = diag(l)^-1 O_i; a lane holds 4 consecutive channels per accumulator quad
     if (row_counts) {
         const float l_tot = sum_across_halves(l);

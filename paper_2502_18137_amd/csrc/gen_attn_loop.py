@@ -93,8 +93,7 @@ class Cfg:
         nxt += 5
         self.O = nxt + (nxt & 1)                  # tuples start at even registers
         self.Q = self.O + 16 * self.NDT
-        self.LT = self.Q + 4 * self.NSTEP         # sum of the last tile's P~, not yet in L
-        self.NVGPR = self.LT + 1
+        self.NVGPR = self.Q + 4 * self.NSTEP
         assert self.NVGPR <= 256
         # ---- SGPRs (pinned) ----
         names = ("u jpart kb0 kb1 vb0 vb1 ldskd ldsvd ldsjl ldsscl lam2 exec pv scx scn jk jv negmagic rt scnn "
@@ -168,12 +167,7 @@ def gen_step(c, o, cur, NST, kbuf, vbuf, masked, pv, dkbuf, dvbuf, label, late):
     x = lambda e: XS + e
     F = lambda e: ops.append((f"v_fma_f32 v{x(e)}, v{x(e)}, s{s['scx']}, v{c.CX}", 1))
     E = lambda e: ops.append((f"v_exp_f32 v{x(e)}, v{x(e)}", 2))
-    # The row sum takes a tile's own sum as one addition, and takes it where the next tile's sum begins: 32 additions a
-    # tile in all, where the softmax has always had them (the same additions with that one behind element 31 instead made
-    # the dense loop 0.9 % slower at d = 128: 2207 against 2187 us at 24 x 22272 x 128, half the blocks kept).
-    def A(e):
-        dst, a_, b_ = ((c.L, c.L, c.LT), (c.LT, x(0), x(1)))[e] if e < 2 else (c.LT, c.LT, x(e))
-        ops.append((f"v_add_f32 v{dst}, v{a_}, v{b_}", 1))
+    A = lambda e: ops.append((f"v_add_f32 v{c.L}, v{c.L}, v{x(e)}", 1))
     if c.fp8:   # two E4M3 values into the low or the high half of a register
         C = lambda w: ops.append((f"v_cvt_pk_fp8_f32 v{XP + w // 2}, v{x(2 * w)}, v{x(2 * w + 1)}"
                                   + (" op_sel:[0,0,1]" if w % 2 else ""), 1))
@@ -378,8 +372,6 @@ def gen_step(c, o, cur, NST, kbuf, vbuf, masked, pv, dkbuf, dvbuf, label, late):
             f"v_exp_f32 v{T0}, v{T0}",
             f"v_mov_b32 v{c.MR}, v{c.MT}",
             "s_nop 0",
-            f"v_add_f32 v{c.L}, v{c.L}, v{c.LT}",          # (what the row sum is still owed belongs to the old reference)
-            f"v_mov_b32 v{c.LT}, 0",
             f"v_mul_f32 v{c.L}, v{c.L}, v{T0}",
             f"v_mov_b32 v{c.FO}, v{T0}",
             f"s_mov_b64 {sp(s, 'hf0')}, -1",
@@ -414,7 +406,6 @@ def gen_loop(c, NST):
     o(f"s_cselect_b64 {sp(s, 'ex0')}, -1, 0")
     o(f"s_mov_b64 {sp(s, 'exp0')}, 0")                 # nothing is pending: iteration 0 has no P~V
     o(f"s_mov_b64 {sp(s, 'hf0')}, 0")
-    o(f"v_mov_b32 v{c.LT}, 0")
     o(f"v_mov_b32 v{c.PJ}, s{s['ldsjl']}")
     o(f"v_mov_b32 v{c.PS}, s{s['ldsscl']}")
     o("s_waitcnt vmcnt(0) lgkmcnt(0)")
@@ -464,14 +455,13 @@ def gen_loop(c, NST):
         for i in ins:
             o(i)
     o("L_exit_%=:")
-    o(f"v_add_f32 v{c.L}, v{c.L}, v{c.LT}")
     o("s_waitcnt vmcnt(0)")                    # no copy of this wave may still be writing LDS
     o("s_nop 7"); o("s_nop 7"); o("s_nop 7")   # the last MFMA results have landed
     return lines
 
 
 def clobbers(c):
-    v = list(range(c.RG, c.RG + 4 * RING)) + list(range(c.T, c.T + 3)) + [c.CX, c.L3, c.PJ, c.PS, c.LT]
+    v = list(range(c.RG, c.RG + 4 * RING)) + list(range(c.T, c.T + 3)) + [c.CX, c.L3, c.PJ, c.PS]
     sg = [c.sg[n] for n in ("negmagic rt scnn t0 t1 a0 a1 b0 b1 jn mlim ex0 ex1 exp0 exp1 hf0 hf1").split()]
     return [f"v{i}" for i in v] + [f"s{i}" for i in sg] + ["vcc", "scc", "memory"]
 
