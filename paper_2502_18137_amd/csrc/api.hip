@@ -632,10 +632,11 @@ int sparge_tune_workspace_bytes(const sparge_desc* desc, int n_inputs, size_t* b
     int rc = check_desc(desc, &s);
     if (rc) return rc;
     if (n_inputs < 1 || !bytes) return fail(SPARGE_EINVAL, "n_inputs must be >= 1 and bytes not NULL");
-    // a forward pass' workspace and the full-attention output per input, one output more (spans of the caller's strides)
+    // a forward pass' workspace and the full-attention output per input, one output more (spans of the caller's strides);
+    // where batches or heads overlap (stride 0), what the search keeps packed is larger than those spans
     const size_t span = (size_t)(s.B - 1) * s.sb + (size_t)(s.H - 1) * s.sh + (size_t)(s.N - 1) * s.sn + s.d;
     const size_t out = align256(span * sizeof(uint16_t));
-    *bytes = (align256(plan(s, SPARGE_WS_FORWARD).total) + out) * n_inputs + out;
+    *bytes = std::max((align256(plan(s, SPARGE_WS_FORWARD).total) + out) * n_inputs + out, tune_layout(s, n_inputs, true).total);
     return SPARGE_OK;
 }
 

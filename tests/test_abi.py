@@ -108,6 +108,47 @@ assert rc == -3 and b"host memory" in lib.sparge_last_error(), (rc, lib.sparge_l
     assert r.returncode == 0, r.stdout + r.stderr
 
 
+def test_search_accepts_the_workspace_it_names():
+    """sparge_tune_workspace_bytes is enough for every layout the library takes, overlapping batches and heads (stride 0)
+    among them, and so is the batched size.  (The call gets past the workspace check and ends at its host tables, which do
+    not fit: nothing is enqueued and no GPU is needed.)"""
+    import subprocess
+    import sys
+    code = """
+import ctypes, resource
+import paper_2502_18137_amd as sp
+from paper_2502_18137_amd.binding import _Desc
+lib = sp.load_library()
+one, ptr = (ctypes.c_float * 1)(0.5), (ctypes.c_void_p * 3)(4096, 4096, 4096)
+shapes = [(B, H, N, d, pv, n) for B, H in ((1, 128), (4, 64)) for N in (1, 333, 1536, 8192) for d in (64, 128)
+          for pv in (0, 1) for n in (1, 3)]
+lams = {}
+for H in (64, 128):
+    m = (1 << 31) // (16 * H)                           # a table of 2 GiB
+    lams[H] = (ctypes.c_float * m).from_buffer(bytearray(bytes([0, 0, 128, 191]) * m))
+res = (ctypes.c_float * 128)()
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (1 << 30),) * 2)
+def call(desc, n, H, size):
+    rc = lib.sparge_tune(ptr, ptr, ptr, n, ctypes.byref(desc), one, 1, one, 1, lams[H], len(lams[H]), 0.1, 0.1, 0.0, 0, res, res, res,
+                         None, None, None, None, ctypes.c_void_p(4096), size, None)
+    return rc, lib.sparge_last_error()
+for B, H, N, d, pv, n in shapes:
+    for sb, sh, sn in ((H * N * d, N * d, d), (N * H * d, d, H * d), (0, N * d, d), (H * N * d, 0, d), (0, 0, d), (2 * H * N * d, N * d + 64, d)):
+        desc = _Desc(B, H, N, d, 1, sb, sh, sn, pv, 0)
+        for f in (lib.sparge_tune_workspace_bytes, lib.sparge_tune_workspace_batched_bytes):
+            size = ctypes.c_size_t(0)
+            assert f(ctypes.byref(desc), n, ctypes.byref(size)) == 0
+            rc, err = call(desc, n, H, size.value)
+            assert rc == -3 and b"host memory" in err, (B, H, N, d, pv, n, sb, sh, sn, rc, err)
+        rc, err = call(desc, n, H, 1 << 10)
+        assert rc == -3 and b"workspace has" in err, (rc, err)
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="", PYTHONPATH=ROOT)
+    r = subprocess.run([sys.executable, "-c", code], env=env, cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
 def test_missing_library_fails_loudly(monkeypatch):
     import paper_2502_18137_amd.binding as b
     monkeypatch.setattr(b, "_LIB", None)

@@ -166,3 +166,26 @@ def test_settings_of_one_launch_equal_settings_one_by_one(sp, B, H, N, d, causal
     assert np.array_equal(got["stage1"], whole["stage1"]) and np.array_equal(got["stage2"], whole["stage2"])
     assert all(got[k] == whole[k] for k in ("tau", "theta", "lam", "sparsity", "l1"))
     assert N < 300 or len(np.unique(whole["stage1"][..., 0, 0])) > 3      # (a single key block is always kept)
+
+
+def test_broadcast_batches_in_the_workspace_that_the_library_names(sp, monkeypatch):
+    """Batches that share their tensors (stride 0): the search runs in sparge_tune_workspace_bytes and finds what it finds
+    on copies of them."""
+    import ctypes
+    import torch
+    from paper_2502_18137_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(5)
+    B, H, N, d = 3, 2, 700, 64
+    one = [tuple((torch.randn(1, H, 6, d, generator=g, device="cuda").repeat_interleave(128, 2)[:, :, :N]
+                  + 0.5 * torch.randn(1, H, N, d, generator=g, device="cuda")).to(torch.bfloat16) for _ in range(3)) for _ in range(2)]
+    grids = ([0.5, 0.9], [0.2, 0.6], [-8.0, -4.0])
+    want = sp.sparge_tune([tuple(t.expand(B, -1, -1, -1).contiguous() for t in x) for x in one], *grids, 0.2, 0.25)
+    shared = [tuple(t.expand(B, -1, -1, -1) for t in x) for x in one]
+    desc, need = binding._desc(shared[0][0]), ctypes.c_size_t(0)
+    assert desc.stride_b == 0
+    assert sp.load_library().sparge_tune_workspace_bytes(ctypes.byref(desc), 2, ctypes.byref(need)) == 0
+    empty = torch.empty
+    monkeypatch.setattr(torch, "empty", lambda n, **k: empty(need.value, **k))
+    got = sp.sparge_tune(shared, *grids, 0.2, 0.25)
+    monkeypatch.undo()
+    assert np.array_equal(got["stage1"], want["stage1"]) and np.array_equal(got["stage2"], want["stage2"])
