@@ -198,13 +198,18 @@ hipError_t launch_attn(const void* Qp, const void* Kp, const float* q_scale, con
                        const AttnStart& start, hipStream_t st);
 // Calls of few Q blocks: the same loop with a 32-row group per workgroup (attn_split.hip), the same bits.
 // attn_split_pays: a compute unit holds one workgroup of it, which runs a group's tiles in a half to two thirds of the
-// time attn.hip needs; so it is worth it while every group has a unit (us, attn.hip / this, the attention alone):
-//   16 x 70 x 64 7.4 / 4.8, 8 x 1024 x 64 16.9 / 9.4, 2 x 4096 x 64 36.9 / 21.0, 1 x 8192 x 64 50.4 / 28.5; with d = 128
-//   8.6 / 5.9, 20.2 / 11.9, 43.6 / 28.1, 58.5 / 37.1; beyond it, 12 x 1024 x 128 20.7 / 21.4, 4 x 4096 x 128 46.6 / 51.9.
-// Causal groups start with the longest, and the second ones a unit gets are the short ones: up to two per unit, while
-// rows are short (16 x 1024 16.8 / 12.8 at d = 64, 19.9 / 16.2 at 128; 4 x 4096 36.2 / 29.8, 43.9 / 40.4; beyond it
-// 2 x 5000 x 128 45.2 / 46.8; 20 x 1024 17.3 / 18.8, 20.1 / 24.8; not with the 16-bit Q K^T at d = 128, whose K tiles fill
-// the LDS: 4 x 4096 54.7 / 58.3, one per unit 2 x 4096 53.6 / 39.4).
+// time attn.hip needs; so it is worth it while every group has a unit (us, attn.hip / this, the attention alone, d = 64 and 128):
+//   16 x 70 7.4 / 5.2, 8.5 / 6.0; 8 x 1024 16.8 / 9.7, 20.1 / 11.7; 2 x 4096 36.8 / 20.6, 43.6 / 28.1; 1 x 8192 49.8 / 27.5,
+//   58.1 / 36.3; FP8 P~V 1 x 8192 52.5 / 26.3, 57.9 / 31.3; 16-bit Q K^T 57.0 / 31.7, 72.4 / 50.5.
+// Beyond it, 12 x 1024 16.8 / 17.2, 20.4 / 21.0; 2 x 8192 50.2 / 50.2, 60.7 / 66.8; FP8 17.7 / 17.2, 20.7 / 18.9; 52.5 / 48.2, 59.4 /
+// 58.2 but 51 x 320 10.2 / 12.3, 12.6 / 13.3; 16-bit Q K^T 20.5 / 21.0, 26.2 / 29.3; 57.7 / 55.5, 75.3 / 88.8.
+// Causal groups start with the longest, and the second ones a unit gets can be the short ones.  Up to an eighth more groups
+// than units that pays from rows of 4 blocks on (12 x 700 13.6 / 10.6, 15.9 / 12.3; 24 x 321 10.5 / 9.1, 11.8 / 10.5; rows of 2
+// blocks 66 x 128 7.9 / 9.0, 9.1 / 10.7), up to half as many again from 8 blocks on (24 x 512 12.2 / 11.1, 14.2 / 12.7; 15 x 800
+// 15.3 / 14.2, 17.9 / 17.6; shorter ones 34 x 321 10.5 / 11.0, 11.9 / 12.6) and up to two a unit where rows are long or an
+// XCD's range is whole heads (5 x 3000 29.3 / 25.9, 34.3 / 32.1; 16 x 1024 17.6 / 14.1, 20.5 / 17.0; else 14 x 1100 18.1 / 18.7, 21.3 /
+// 23.9; 10 x 1500 25.6 / 27.4 at 128; 128 x 128 8.1 / 9.7, 9.5 / 11.4); rows beyond 64 blocks 2 x 5000 x 128 45.2 / 46.8.  Not
+// with the 16-bit Q K^T at d = 128, whose K tiles fill the LDS: 4 x 4096 64.6 / 65.8 with every block kept.
 constexpr int SPLIT_MAX_TN = 256;    // key blocks its lists hold
 bool attn_split_pays(const Shape& s, int causal);
 hipError_t launch_attn_split(const void* Qp, const void* Kp, const float* q_scale, const float* k_scale,
