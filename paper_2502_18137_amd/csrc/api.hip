@@ -776,7 +776,7 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
             Shape x = launch_shape((stage1 ? k_n : 1) * G, G);
             x.by_setting = stage1;
             if ((e = launch_topcdf(logits(n), sim_q(n), sim_k(n), x, tp, thp, causal, mask, st)) != hipSuccess) return hip_fail(e, "topcdf");
-            if ((r = attend(dense && G == n_inputs, k0, k_n, b_n, n, G, !stage1, lp, !stage1))) return r;
+            if ((r = attend(dense && G == n_inputs, k0, k_n, b_n, n, G, !stage1, lp, !stage1 && t.settings > 1))) return r;
             x = launch_shape(k_n * G, G);
             if ((e = launch_rel_l1(o_cur, o_ref(n), x, sums_at(k0, n), st)) != hipSuccess) return hip_fail(e, "rel_l1");
         }
@@ -856,7 +856,8 @@ int sparge_tune(const void* const* Q, const void* const* K, const void* const* V
         const int b_n = std::min(t.batch, n_lambda - c0);
         for (int k0 = 0; k0 < b_n; k0 += t.settings) {
             const int k_n = std::min(t.settings, b_n - k0);
-            for (int k = 0; k < k_n; ++k) lp.v[k] = lambda_grid[c0 + k0 + k];
+            if (t.settings == 1) std::fill(lp.v, lp.v + SPARGE_MAX_HEADS, lambda_grid[c0 + k0]);   // an ordinary attention launch
+            else for (int k = 0; k < k_n; ++k) lp.v[k] = lambda_grid[c0 + k0 + k];
             if ((rc = run(false, false, tp, thp, lp, k0, k_n, b_n))) return rc;
         }
         if ((rc = collect(b_n, &t2[(size_t)c0 * H * 2]))) return rc;

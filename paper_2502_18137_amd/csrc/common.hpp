@@ -12,6 +12,18 @@ constexpr int BQ = SPARGE_BQ;         // query rows per block (Alg. 1 line 2; Ap
 constexpr int BK = SPARGE_BK;         // key rows per block
 constexpr int RG = SPARGE_ROW_GROUP;  // rows per stage-2 row group (b_q / c_w)
 
+// (batch, head) pair whose operands pair bh uses; index of its per-head parameters, `own`: pair behind the dense ones.  The
+// divisions stay behind branches that an ordinary call never takes.
+__host__ __device__ inline int operand_of(int bh, int op_bh) {
+    if (bh < op_bh) return bh;
+    asm volatile("");
+    return bh % op_bh;
+}
+__host__ __device__ inline int param_of(int own, int h, int by_setting, int op_bh) {
+    if (!by_setting) return h;
+    asm volatile("");
+    return own / op_bh;
+}
 struct Shape {
     int B, H, N, d, dtype;
     long long sb, sh, sn;  // element strides of the 16-bit tensors
@@ -26,8 +38,8 @@ struct Shape {
     int by_setting;        // the per-head parameters (tau, theta, lambda) are one value per setting instead
     int one_mask;          // the mask has op_bh pairs: one for all settings
 
-    __host__ __device__ int operand(int bh) const { return bh < op_bh ? bh : bh % op_bh; }
-    __host__ __device__ int param(int own, int h) const { return by_setting ? own / op_bh : h; }   // own: pair behind the dense ones
+    __host__ __device__ int operand(int bh) const { return operand_of(bh, op_bh); }
+    __host__ __device__ int param(int own, int h) const { return param_of(own, h, by_setting, op_bh); }
 };
 
 // Per-head scalars travel to the device inside the kernel argument block.
