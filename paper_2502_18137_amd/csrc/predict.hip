@@ -288,13 +288,15 @@ __device__ __forceinline__ double wave_max(double v) {
 // the threshold, so one cut in the ranking decides the row.  Keys (see topcdf_kernel) rank the entries by one 64-bit
 // comparison; lane L holds those of key blocks 64 e + L.  The cut is bracketed between two keys -- the mass from `lo` on
 // reaches the threshold, the mass from `hi` on does not -- and the bracket halved until at most FEW entries lie in it; those
-// are ranked one by one.  Keys differ, so that ends after at most 64 halvings; the first probe is the smallest
-// probability the cut can have when nothing else is known (all that ranks from the cut on is more than (1 - tau) of the
-// mass), which leaves the few octaves below the row's maximum.
+// are ranked one by one, two lanes an entry.  The first probe is the smallest probability the cut can have when nothing else is
+// known (all that ranks from the cut on is more than (1 - tau) of the mass), which leaves the few octaves below the row's
+// maximum.  Once two probes have left no entry out, the bracket shrinks to the keys in it; entries that are equal up to
+// their index then (repeated or padded tokens: halving alone would take 50 probes to tell them apart) rank by it at once.
 // What bounds it is the vector ALU (16 rows a SIMD at 32 x 65536): a probe costs EPL comparisons, selections and fp64
 // additions a lane and one reduction, five to eight of them a row, where a bitonic sort of the row in registers
-// ran 55 stages at EPL = 16: 60 against 151 us at 32 x 65536, 26 against 43 us at 48 x 17550 (EPL = 8), 29 against
-// 84 us at 32 x 32768 causal; no difference where the launch is one wave's latency (EPL = 2, 4).
+// ran 55 stages at EPL = 16.  Sort / this, random keys: 169 / 82 us at 32 x 65536, 32 / 19 at 48 x 17550 (EPL = 8), 35 / 22 at
+// 32 x 32768 causal; with all keys equal 145 / 60, half of them 166 / 103 (190 and 178 by halving alone).  Where the launch
+// is one wave's latency: EPL = 1 7.8 / 6.8, EPL = 2 11.7 / 12.3, EPL = 4 no difference.
 // The ranks cover the n key blocks that the row sees (n <= 64 EPL); the others are 0 in the mask.
 // row_at(j): the row's logit of key block j < n; cand: 2 FEW doubles of LDS of this wave's own (may be where row_at reads
 // from: all logits are read before the first candidate is written).
@@ -354,8 +356,26 @@ __device__ __forceinline__ void topcdf_row(RowAt row_at, const int i, const doub
     int n_lo = n, n_hi = 0;                                      // entries from lo, from hi on
     double mass_hi = 0.0;                                        // mass from hi on
     u64 mid = bits(uniform_f64((1.0 - tau) * tot * __builtin_amdgcn_rcp(static_cast<double>(n)) * 0.999));
+    int idle = 0;          // probes that left no entry out
+    bool equal = false;    // the bracket's entries are equal up to their index
 #pragma unroll 1
     while (n_lo - n_hi > FEW && hi - lo > 1) {
+        if (idle == 2) {   // shrink it to the keys in it
+            idle = 0;
+            double least = NEG, most = NEG;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) {
+                const bool in = key[e] >= lo && key[e] < hi && key[e] != 0;
+                const double k = __longlong_as_double(static_cast<long long>(key[e]));
+                least = fmax(least, in ? -k : NEG);
+                most = fmax(most, in ? k : NEG);
+            }
+            least = -uniform_f64(wave_max(least)), most = uniform_f64(wave_max(most));
+            if (!(least < most)) break;   // (a row of NaN: no key is in it)
+            lo = bits(least), hi = bits(most) + 1;
+            equal = ((lo ^ (hi - 1)) >> 16) == 0;
+            if (equal) break;
+        }
         if (mid <= lo || mid >= hi) mid = lo + (hi - lo) / 2;
         double m = 0.0;
         int c = 0;
@@ -366,45 +386,69 @@ __device__ __forceinline__ void topcdf_row(RowAt row_at, const int i, const doub
             c += __popcll(__builtin_amdgcn_ballot_w64(ge));
         }
         m = uniform_f64(group_sum<64>(m));
+        idle += c == (m >= thresh ? n_lo : n_hi);
         if (m >= thresh) lo = mid, n_lo = c;
         else hi = mid, n_hi = c, mass_hi = m;
         mid = 0;
     }
-    // 4. the entries in it, one per lane: kept iff the mass before them is below the threshold; the smallest kept key is
-    // the cut (an entry without mass is never kept)
-    int few = 0;
+    u64 from = hi;            // the cut: entries with keys from here on are kept,
+    unsigned int kept_e = 0;  // and (bit e) those of equal ones that rank before it
+    if (equal) {
+        double each = NEG;
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) {
-        const bool in = key[e] >= lo && key[e] < hi && key[e] != 0;
-        const u64 bal = __builtin_amdgcn_ballot_w64(in);
-        if (in) {
-            const int at = few + __popcll(bal & ((1ull << lane) - 1ull));
-            cand[2 * at] = __longlong_as_double(static_cast<long long>(key[e]));
-            cand[2 * at + 1] = p[e];
+        for (int e = 0; e < EPL; ++e) each = fmax(each, key[e] >= lo && key[e] < hi ? p[e] : NEG);
+        each = uniform_f64(wave_max(each));
+        int before = 0;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {   // ascending by index
+            const bool in = key[e] >= lo && key[e] < hi;
+            const u64 bal = __builtin_amdgcn_ballot_w64(in);
+            const int r = before + __popcll(bal & ((1ull << lane) - 1ull));
+            kept_e |= static_cast<unsigned int>(in && each > 0.0 && mass_hi + r * each < thresh) << e;
+            before += __popcll(bal);
         }
-        few += __popcll(bal);
+    } else {
+        // 4. the entries in it, one per lane: kept iff the mass before them is below the threshold; the smallest kept key is
+        // the cut (an entry without mass is never kept)
+        int few = 0;
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) {
+            const bool in = key[e] >= lo && key[e] < hi && key[e] != 0;
+            const u64 bal = __builtin_amdgcn_ballot_w64(in);
+            if (in) {
+                const int at = few + __popcll(bal & ((1ull << lane) - 1ull));
+                cand[2 * at] = __longlong_as_double(static_cast<long long>(key[e]));
+                cand[2 * at + 1] = p[e];
+            }
+            few += __popcll(bal);
+        }
+        __builtin_amdgcn_wave_barrier();   // (written and read by this wave only, whose LDS accesses complete in order)
+        static_assert(FEW == 32, "two lanes per candidate, each adds up every other one of those before it");
+        const double my_key = cand[2 * (lane & 31)], my_p = cand[2 * (lane & 31) + 1];
+        double before = 0.0;
+#pragma unroll 8
+        for (int c = 0; c < few; c += 2) {
+            const double2 x = reinterpret_cast<const double2*>(cand)[c + (lane >> 5)];   // (one behind the last may be read)
+            before += c + (lane >> 5) < few && x.x > my_key ? x.y : 0.0;
+        }
+        before = mass_hi + add_partner<32>(before);
+        const bool kept = (lane & 31) < few && my_p > 0.0 && before < thresh;
+        // (keys are positive as fp64 numbers and order alike)
+        const double cut = -uniform_f64(wave_max(kept ? -my_key : NEG));
+        if (cut < -NEG) from = bits(cut);
     }
-    __builtin_amdgcn_wave_barrier();   // (written and read by this wave only, whose LDS accesses complete in order)
-    const double my_key = cand[2 * min(lane, FEW - 1)], my_p = cand[2 * min(lane, FEW - 1) + 1];
-    double before = mass_hi;
-#pragma unroll 4
-    for (int c = 0; c < few; ++c) before += cand[2 * c] > my_key ? cand[2 * c + 1] : 0.0;
-    const bool kept = lane < few && my_p > 0.0 && before < thresh;
-    // (keys are positive as fp64 numbers and order alike)
-    const double cut = -uniform_f64(wave_max(kept ? -my_key : NEG));
-    const u64 from = cut < -NEG ? bits(cut) : hi;
 
     // 5. fix-block overrides and causal rules
 #pragma unroll
     for (int e = 0; e < EPL; ++e) {
         const int j = 64 * e + lane;
-        const bool m = (key[e] >= from && p[e] > 0.0) || (fix >> e & 1) || (causal && j == (i * BQ) / BK);
+        const bool m = (key[e] >= from && p[e] > 0.0) || (kept_e >> e & 1) || (fix >> e & 1) || (causal && j == (i * BQ) / BK);
         if (j < s.Tn) out[j] = j < n && m ? 1 : 0;
     }
     for (int j = 64 * EPL + lane; j < s.Tn; j += 64) out[j] = 0;
 }
-// The same with the fewest entries per lane that hold the row: a causal row of a quarter (half) of the blocks.  Causal predictor call, with the logits tiles left out that no row sees:
-// 428 against 471 us at 32 x 65536 x 128, 365 against 423 us at 8 x 131072 x 128 (TopCdf at 32 x 32768: 75 against 108 us).
+// The same with the fewest entries per lane that hold the row: a causal row of a quarter (half) of the blocks.  Predictor call
+// without / with that, causal: 382 / 375 us at 32 x 65536 x 128, 206 / 192 at 8 x 131072 x 64, 78 / 76 at 48 x 17550 x 64.
 template <int EPL, class RowAt>
 __device__ __forceinline__ void topcdf_row_of(RowAt row_at, const int i, const double sim_q_i, const double* __restrict__ sk,
                                               const Shape& s, const double tau, const double theta, const int causal,
