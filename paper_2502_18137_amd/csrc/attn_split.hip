@@ -20,7 +20,7 @@
 // us; V copied between the products at d = 64 too, 1.22 us.
 // Everything that is decided or rounded per tile is decided and rounded as in attn.hip, and every sum has its order (P~ V:
 // tiles in list order on the same matrix instruction; l: one P~ after the other through all tiles), so the two kernels
-// give the same bits and the choice between them is one of speed alone (attn_split_pays).
+// give the same bits, infinities and NaN included (of a NaN: that it is one), and the choice between them is one of speed alone (attn_split_pays).
 #include "attn_ops.hpp"
 
 namespace sparge {
@@ -126,7 +126,9 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     // A causal group runs only the tiles it sees (the other ones of its block change nothing).
     const int jmax = CAUSAL ? min(s.Tn, (i * BQ + BQ - 1) / BK + 1) : s.Tn;
     const int jvis = CAUSAL ? min(jmax, (g * RG + RG - 1) / BK + 1) : jmax;
-    int listed = 0, cnt = 0;   // kept blocks of the Q block; those that this group sees
+    // (the loop of attn.hip takes key blocks from j_rag on, and the one before them, with element masks)
+    const int j_rag = CAUSAL ? min(s.N / BK, 2 * i) : s.N / BK;
+    int listed = 0, cnt = 0, full = 0;   // kept blocks of the Q block; those that this group sees; those before j_rag
     {
         static_assert(SPLIT_MAX_TN == 64 * NW, "one flag per lane and wave");
         // (loads without conditions and in one block, all in flight together; without a mask they read what they like)
@@ -150,6 +152,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
             }
             listed += __popcll(bal);
             cnt += __popcll(__builtin_amdgcn_ballot_w64(keep && j < jvis));
+            full += __popcll(__builtin_amdgcn_ballot_w64(keep && j < j_rag));
         }
     }
     if (wave == NW && lane < 4 * NW) jl[listed + lane] = 0;   // copies behind the list fetch a tile nobody reads
@@ -249,6 +252,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
                     m_loc = (__int_as_float(max(m0, m1)) - BIAS) * sc;
                 }
                 m_loc = max_across_halves(m_loc);
+                if (t0 + wave == 0) m_loc = fmaxf(m_loc, NEG);   // (scores that are all NaN: the running maximum starts at -inf)
             }
             if (!live && wave == 1 && t0 > 0) add_tile(t0 - NW + 1);
             if (hl == 0) row_max[l32][wave] = m_loc;
@@ -272,7 +276,8 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
             if (live) {
                 float cx = __builtin_fmaf(-BIAS, sc, -ref_own);
                 if constexpr (FP8) cx += 6.807354927062988f;   // P~ scaled by 448 / 2^2: log2(448) - 2
-                if (ref_own == NEG) cx = 0.f;                  // a row that has seen no key yet: its scores are all -inf
+                // a row that has seen no key yet: its masked scores are all -inf (and scores of -inf themselves give NaN)
+                if (ref_own == NEG && t0 + wave + 1 >= full) cx = 0.f;
 #pragma unroll
                 for (int e = 0; e < 32; ++e)
                     p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(__int_as_float(S[e >> 4][e & 15]), sc, cx));
@@ -444,6 +449,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int w = 0; w < NW; ++w)
             votes |= (__builtin_amdgcn_ballot_w64(row_counts && ml[w] - m[w] > lam2) != 0) << w;
+        if (t0 == 0) votes |= __builtin_amdgcn_ballot_w64(row_counts && ml[0] != NEG) != 0;   // (+inf among them)
         float f[NW];
         int moved = 0;
         if (any_move) {

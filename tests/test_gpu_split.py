@@ -42,3 +42,50 @@ def test_a_head_of_its_own_equals_the_head_of_a_large_call(d, dtype, causal, kw)
             assert torch.equal(o, O[b:b + 1, h:h + 1]), (N, b, h)
             assert torch.equal(st, stats[b:b + 1, h:h + 1]), (N, b, h)
     assert skipped > 0
+
+
+def not_finite(kind, Q, K, V, N):
+    """The kinds of infinities and NaN that scores, their maxima and P~ can meet (Q, K, V changed in place)."""
+    inf, nan = float("inf"), float("nan")
+    if kind == "K has infinities":
+        K[:, :, 3, 5], K[:, :, N // 2, 5], K[:, :, N - 1, 9] = inf, -inf, inf
+    elif kind == "NaN":
+        K[:, :, N // 3, 7] = Q[:, :, N // 2, 2] = V[:, :, N - 1, 3] = nan
+    elif kind == "a key block of NaN":
+        K[:, :, :64] = nan
+    elif kind == "Q rows of infinite scores":
+        Q[:, :, ::37, 2] = inf
+    elif kind == "all scores infinite":
+        Q[..., 2] = inf
+    elif kind == "first key blocks at -inf":
+        Q[..., 1] = Q[..., 1].abs() + 0.5
+        K[:, :, :200, 1] = -inf
+    elif kind == "infinite V":
+        V[:, :, 5, 3], V[:, :, N // 2, 4] = inf, -inf
+
+
+@pytest.mark.parametrize("kw", [{}, {"pv_fp8": True}, {"qk16": True}], ids=["int8", "fp8", "qk16"])
+@pytest.mark.parametrize("kind", ["K has infinities", "NaN", "a key block of NaN", "Q rows of infinite scores", "all scores infinite",
+                                  "first key blocks at -inf", "infinite V"])
+def test_infinities_and_nan_come_out_the_same(kind, kw):
+    import torch
+    import paper_2502_18137_amd as sp
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    for N, d, dt in ((100, 64, torch.bfloat16), (333, 128, torch.float16), (1100, 64, torch.float16), (1100, 128, torch.bfloat16)):
+        groups, Tm, Tn = (N + 31) // 32, (N + 127) // 128, (N + 63) // 64
+        H = min(2 * units // groups + 1, 128)
+        B = -(-(2 * units // groups + 1) // H)
+        g = torch.Generator(device="cuda").manual_seed(N + d)
+        Q, K, V = (torch.randn(B, H, N, d, generator=g, device="cuda").to(dt) for _ in range(3))
+        not_finite(kind, Q, K, V, N)
+        masks = (None, (torch.rand(B, H, Tm, Tn, generator=g, device="cuda") < 0.6).to(torch.uint8))
+        for causal in (False, True):
+            for mask in masks:
+                print(f"{kind}: B={B} H={H} N={N} d={d} {dt} causal={causal} mask={mask is not None} {kw}", flush=True)
+                args = dict(causal=causal, return_stats=True, **kw)
+                O, stats = sp.sparge_attn(Q, K, V, mask, -3.0, **args)
+                one = [t[:1, :1].contiguous() for t in (Q, K, V)]
+                o, st = sp.sparge_attn(*one, None if mask is None else mask[:1, :1].contiguous(), -3.0, **args)
+                assert torch.equal(st, stats[:1, :1])
+                same = (o == O[:1, :1]) | (o.isnan() & O[:1, :1].isnan())
+                assert same.all(), (kind, N, d, causal, int((~same).sum()))
