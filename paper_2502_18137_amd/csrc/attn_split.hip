@@ -122,7 +122,7 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
                           : *reinterpret_cast<const v4i*>(static_cast<const int8_t*>(a.Qp) +
                                                           ((long long)op * s.N + qrow) * D + st * 32 + hl * 16);
     }
-    // ---- the Q block's kept key blocks in ascending order: every wave counts all of them, the first four write a quarter.
+    // ---- the Q block's kept key blocks in ascending order: every wave counts all of them, the first two write a half.
     // A causal group runs only the tiles it sees (the other ones of its block change nothing).
     const int jmax = CAUSAL ? min(s.Tn, (i * BQ + BQ - 1) / BK + 1) : s.Tn;
     const int jvis = CAUSAL ? min(jmax, (g * RG + RG - 1) / BK + 1) : jmax;
@@ -130,18 +130,19 @@ __global__ __launch_bounds__(128 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_
     const int j_rag = CAUSAL ? min(s.N / BK, 2 * i) : s.N / BK;
     int listed = 0, cnt = 0, full = 0;   // kept blocks of the Q block; those that this group sees; those before j_rag
     {
-        static_assert(SPLIT_MAX_TN == 64 * NW, "one flag per lane and wave");
+        constexpr int NL = SPLIT_MAX_TN / 64;   // flags a lane
+        static_assert(NL == 2 && SPLIT_MAX_TN == 64 * NL, "two loads in one block below");
         // (loads without conditions and in one block, all in flight together; without a mask they read what they like)
         const bool dense = !a.mask || own < 0;
         const uint8_t* mrow = dense ? a.v_tiles : a.mask + ((long long)(s.one_mask ? op : own) * s.Tm + i) * s.Tn;
-        unsigned int mk[NW];
+        unsigned int mk[NL];
 #pragma unroll
-        for (int q = 0; q < NW; ++q) mk[q] = mrow[min(q * 64 + lane, jmax - 1)];
-        const float sc = QK16 ? 1.f : a.k_scale[(long long)op * s.Tn + min((wave & (NW - 1)) * 64 + lane, jmax - 1)];
+        for (int q = 0; q < NL; ++q) mk[q] = mrow[min(q * 64 + lane, jmax - 1)];
+        const float sc = QK16 ? 1.f : a.k_scale[(long long)op * s.Tn + min((wave & (NL - 1)) * 64 + lane, jmax - 1)];
         const float qs = (QK16 ? 1.f : a.q_scale[(long long)op * s.Tm + i]) * a.sm_scale * LOG2E;
-        asm volatile("" ::"v"(mk[0]), "v"(mk[1]), "v"(mk[2]), "v"(mk[3]), "v"(sc), "v"(qs), "v"(lam2));
+        asm volatile("" ::"v"(mk[0]), "v"(mk[1]), "v"(sc), "v"(qs), "v"(lam2));
 #pragma unroll
-        for (int q = 0; q < NW; ++q) {
+        for (int q = 0; q < NL; ++q) {
             const int j = q * 64 + lane;
             const bool keep = (dense || mk[q] != 0) && j < jmax;
             const unsigned long long bal = __builtin_amdgcn_ballot_w64(keep);

@@ -222,7 +222,7 @@ hipError_t launch_attn(const void* Qp, const void* Kp, const float* q_scale, con
 // XCD's range is whole heads (5 x 3000 29.3 / 25.9, 34.3 / 32.1; 16 x 1024 17.6 / 14.1, 20.5 / 17.0; else 14 x 1100 18.1 / 18.7, 21.3 /
 // 23.9; 10 x 1500 25.6 / 27.4 at 128; 128 x 128 8.1 / 9.7, 9.5 / 11.4); rows beyond 64 blocks 2 x 5000 x 128 45.2 / 46.8.  Not
 // with the 16-bit Q K^T at d = 128, whose K tiles fill the LDS: 4 x 4096 64.6 / 65.8 with every block kept.
-constexpr int SPLIT_MAX_TN = 256;    // key blocks its lists hold
+constexpr int SPLIT_MAX_TN = 128;    // key blocks its lists hold: a head of 256 row groups has no more
 bool attn_split_pays(const Shape& s, int causal);
 hipError_t launch_attn_split(const void* Qp, const void* Kp, const float* q_scale, const float* k_scale,
                              const void* v_tiles, const float* v_scale, const Shape& s, const uint8_t* mask,
