@@ -1,14 +1,31 @@
 """Calls of few row groups run the flash loop with a workgroup per 32-row group whose waves share the group's tiles
-(attn_split.hip); larger calls give a row group to one wave (attn.hip).  Both decide, round and add in the same order, so a
-head in a call of its own must come out as the same head of a call that is too large for the shared form, bit for bit:
-output and execution counters.  Sizes at the edges of a row group, a key block, a round of four tiles and the longest
-list (256 key blocks); random masks with rows that keep nothing, scores wide enough for the reference maximum to move and for
-the stage-2 test to skip."""
+(attn_split.hip); larger calls give a row group to one wave (attn.hip).  Both decide, round and add in the same order, so heads
+in a call of their own must come out as the same heads of a call that is too large for the shared form, bit for bit:
+output and execution counters.  Sizes at the edges of a row group, a key block, a round of four tiles, the longest list (as
+many row groups as there are compute units in one head) and the causal lines beyond it; random masks with rows that keep
+nothing, scores wide enough for the reference maximum to move and for the stage-2 test to skip."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
-SIZES = [1, 31, 33, 64, 65, 129, 256, 257, 700, 1100, 4173, 16321, 16384]
+
+def shared_form(heads, N, d, causal, qk16, units):
+    """The line between the kernels (attn_split_pays), for the sizes below to lie on the side they are meant for."""
+    Tn, groups = (N + 63) // 64, heads * ((N + 31) // 32)
+    if Tn > 128 or groups <= units:
+        return Tn <= 128
+    if not causal or Tn > 64 or (qk16 and d == 128):
+        return False
+    return (8 * groups <= 9 * units and Tn >= 4 or 2 * groups <= 3 * units and Tn >= 8
+            or groups <= 2 * units and (Tn >= 32 or Tn >= 16 and heads % 8 == 0))
+
+
+def calls(causal, d, qk16, units):
+    """-> (heads, N) of calls that run the shared form."""
+    yield from ((1, N) for N in (1, 31, 33, 64, 65, 129, 256, 257, 700, 1100, 4173, 32 * units - 31, 32 * units))
+    yield from ((3, 700), (units // 2, 60), (8, 4 * units))
+    if causal and not (qk16 and d == 128):
+        yield from ((units // 8 + 1, 250), (3 * units // 32, 509), (16, 4 * units), (8, 8 * units), (5, 3 * 32 * units // 8 + 1))
 
 
 @pytest.mark.parametrize("kw", [{}, {"pv_fp8": True}, {"qk16": True}], ids=["int8", "fp8", "qk16"])
@@ -20,13 +37,14 @@ def test_a_head_of_its_own_equals_the_head_of_a_large_call(d, dtype, causal, kw)
     dt = torch.float16 if dtype == "fp16" else torch.bfloat16
     units = torch.cuda.get_device_properties(0).multi_processor_count
     skipped = 0
-    for N in SIZES:
+    for few, N in calls(causal, d, "qk16" in kw, units):
         groups, Tm, Tn = (N + 31) // 32, (N + 127) // 128, (N + 63) // 64
-        heads = 2 * units // groups + 1                     # one more than the shared form takes, causal or not
+        heads = max(2 * units // groups, few) + 1           # one more than the shared form takes, causal or not
         H = min(heads, 128)
         B = -(-heads // H)
+        assert shared_form(few, N, d, causal, "qk16" in kw, units) and not shared_form(B * H, N, d, causal, "qk16" in kw, units)
         keep, lam = (1.0, -3.0) if N % 2 else (0.4, -1.5)
-        print(f"B={B} H={H} N={N} d={d} {dtype} causal={causal} {kw}", flush=True)
+        print(f"B={B} H={H} few={few} N={N} d={d} {dtype} causal={causal} {kw}", flush=True)
         g = torch.Generator(device="cuda").manual_seed(N + d)
         wide = 1 + 1.5 * torch.randn(B, H, Tn, 1, generator=g, device="cuda").abs().repeat_interleave(64, 2)[:, :, :N]
         Q, K, V = ((torch.randn(B, H, N, d, generator=g, device="cuda") * wide).to(dt) for _ in range(3))
@@ -36,11 +54,11 @@ def test_a_head_of_its_own_equals_the_head_of_a_large_call(d, dtype, causal, kw)
         O, stats = sp.sparge_attn(Q, K, V, mask, lam, **args)
         assert torch.isfinite(O.float()).all()
         skipped += int((stats[..., 3] - stats[..., 1]).sum())
-        for b, h in {(0, 0), (B - 1, H - 1)}:
-            one = tuple(t[b:b + 1, h:h + 1] for t in (Q, K, V, mask.contiguous()))
-            o, st = sp.sparge_attn(*one[:3], one[3].contiguous(), lam, **args)
-            assert torch.equal(o, O[b:b + 1, h:h + 1]), (N, b, h)
-            assert torch.equal(st, stats[b:b + 1, h:h + 1]), (N, b, h)
+        for b, h in {(0, 0), (B - 1, H - few)}:             # `few` heads from there on
+            one = tuple(t[b:b + 1, h:h + few].contiguous() for t in (Q, K, V, mask))
+            o, st = sp.sparge_attn(*one, lam, **args)
+            assert torch.equal(o, O[b:b + 1, h:h + few]), (few, N, b, h)
+            assert torch.equal(st, stats[b:b + 1, h:h + few]), (few, N, b, h)
     assert skipped > 0
 
 
