@@ -1,9 +1,10 @@
 """The library allocates nothing, never synchronises (sparge_tune aside) and sets its counters inside its kernels,
 so a caller may record its calls into a HIP graph.  Recorded here: the whole of Algorithm 1
 (sparge_forward) in its three product variants; every replay, with other eager work and synchronisations
-in between, must reproduce the eager result bit for bit, also after the inputs change in place.  Two sizes: a short call
-(three launches on one stream, no more items than resident workgroups, so no item counters), and one beyond short calls
-(the fork onto the library's second stream and the join are captured, and the items are drawn from counters)."""
+in between, must reproduce the eager result bit for bit, also after the inputs change in place.  Three sizes: short calls
+(three launches on one stream) of so few row groups that each has a workgroup of its own, and of more, but no more items
+than resident workgroups, so no item counters; and one beyond short calls (the fork onto the library's second stream and the
+join are captured, and the items are drawn from counters)."""
 import numpy as np
 import pytest
 
@@ -28,7 +29,7 @@ def assert_forks_and_counts(N, H):
     assert (N + 63) // 64 > 256 and H * ((N + 127) // 128) > 2 * torch.cuda.get_device_properties(0).multi_processor_count
 
 
-@pytest.mark.parametrize("N,H", [(1500, 3), (16500, 4)], ids=["short", "forked"])
+@pytest.mark.parametrize("N,H", [(1500, 3), (1500, 12), (16500, 4)], ids=["few row groups", "short", "forked"])
 @pytest.mark.parametrize("variant", [{}, {"pv_fp8": True}, {"qk16": True}], ids=["int8_16bit", "fp8_pv", "qk16"])
 def test_forward_replays_from_a_graph(sp, variant, N, H):
     import torch
@@ -67,7 +68,7 @@ def test_forward_replays_from_a_graph(sp, variant, N, H):
         assert torch.isfinite(junk)
 
 
-@pytest.mark.parametrize("N,H", [(4000, 6), (16500, 4)], ids=["short", "forked"])
+@pytest.mark.parametrize("N,H", [(4000, 2), (4000, 6), (16500, 4)], ids=["few row groups", "short", "forked"])
 def test_two_graphs_replayed_on_two_streams(sp, N, H):
     """Two captures of sparge_forward, each with its own workspace, outputs and inputs (one causal), replayed at
     the same time on two streams, three rounds with eager launches in between: every replay reproduces its

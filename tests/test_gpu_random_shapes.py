@@ -2,7 +2,8 @@
 density, lambda and the product variant are drawn per case, so that short lists (one to a few tiles),
 ragged tails, rows that lose tiles to lambda and reference-maximum moves meet in combinations the fixed
 cases do not list.  Each case: the GPU loop against the oracle loop on the same mask (bars as in the
-parity tests)."""
+parity tests).  A head of its own runs the kernel for few row groups; the same problem as one of many heads of a large call,
+with other heads of another lambda beside it, strided tensors and no mask where every block is kept, runs the other one."""
 import math
 
 import numpy as np
@@ -38,6 +39,28 @@ def draw(seed):
 
 @pytest.mark.parametrize("seed", range(36))
 def test_random_problem(sp, seed):
+    check_problem(sp, seed, large=False)
+
+
+@pytest.mark.parametrize("seed", range(36))
+def test_random_problem_in_a_large_call(sp, seed):
+    check_problem(sp, seed, large=True)
+
+
+def large_call(Q, K, V, mask, lam, bnhd):
+    """The problem in every head of a call of more than two row groups per compute unit; odd heads skip at another lambda."""
+    import torch
+    heads = 2 * torch.cuda.get_device_properties(0).multi_processor_count // ((Q.shape[2] + 31) // 32) + 1
+    H = min(heads, 128)
+    B = -(-heads // H)
+    def spread(x):
+        x = x.expand(B, H, *x.shape[2:])
+        return x.transpose(1, 2).contiguous().transpose(1, 2) if bnhd else x.contiguous()
+    Q, K, V = (spread(x) for x in (Q, K, V))
+    return Q, K, V, None if mask is None else mask.expand(B, H, -1, -1).contiguous(), [lam if h % 2 == 0 else -0.25 for h in range(H)]
+
+
+def check_problem(sp, seed, large):
     import torch
     N, d, dtype, causal, variant, density, lam, noise = draw(seed)
     print(f"seed {seed}: N={N} d={d} {dtype} causal={causal} {variant} density={density} lambda={lam} noise={noise}",
@@ -52,7 +75,13 @@ def test_random_problem(sp, seed):
     if causal:
         mask[0, 0, np.arange(Tm), np.minimum(2 * np.arange(Tm), Tn - 1)] = 1
     kw = {"pv_fp8": variant == "fp8", "qk16": variant == "qk16"}
-    O, stats = sp.sparge_attn(Q, K, V, torch.from_numpy(mask).to("cuda"), lam, causal=causal, return_stats=True, **kw)
+    args = (Q, K, V, torch.from_numpy(mask).to("cuda"), lam)
+    if large:
+        args = large_call(Q, K, V, None if mask.all() else args[3], lam, bnhd=seed % 2 == 1)
+    O, stats = sp.sparge_attn(*args, causal=causal, return_stats=True, **kw)
+    if large:                                                   # every head of this lambda is the same
+        assert (O[:, ::2] == O[:1, :1]).all() and (stats[:, ::2] == stats[:1, :1]).all()
+        assert (O[:, 1::2] == O[:1, 1:2]).all() and (stats[:, 1::2, [0, 2, 3]] == stats[:1, :1, [0, 2, 3]]).all()
     O = O.float().cpu().numpy().astype(np.float64)[0, 0]
     stats = stats.cpu().numpy()[0, 0]
     assert np.isfinite(O).all()

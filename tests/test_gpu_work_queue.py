@@ -1,7 +1,8 @@
 """Work distribution of the attention kernel: resident workgroups take (head, Q block) items from one counter per
 XCD range and move on to the other ranges when their own is empty.  Cases where that matters: more items than
-resident workgroups, a head count that is no multiple of 8 (ranges cut heads), fewer items than ranges, and
-heads of very different density (one range holds almost all the work, the others finish and take from it).
+resident workgroups, a head count that is no multiple of 8 (ranges cut heads), a last range shorter than the others, and
+heads of very different density (one range holds almost all the work, the others finish and take from it); and calls of
+so few row groups that each has a workgroup of its own and no items are handed out.
 Every output row is checked against the oracle loop on the same mask: an item computed twice, skipped, or
 computed with another item's lists would show."""
 import math
@@ -27,9 +28,11 @@ def sp():
 @pytest.mark.parametrize("H,N,d,causal,dense_heads", [
     (9, 8192, 64, False, (0,)),        # 576 items > 512 resident workgroups; ranges cut heads; head 0 dense
     (16, 4224, 128, False, (3, 4)),    # 528 items; two dense heads in one range
-    (3, 300, 64, True, (1,)),          # 9 items: fewer than 8 ranges of 2
+    (3, 300, 64, True, (1,)),          # 30 row groups: a work-group each, no items
+    (1, 8200, 64, False, (0,)),        # 65 items: seven ranges of 9, one of 2; a work-group per item
     (24, 2944, 128, True, (23,)),      # 552 items, causal, the last range holds the dense head
-    (7, 1700, 64, True, (3,)),         # 98 items, causal: ranges of 13 items against heads of 14 Q blocks (two passes per range)
+    (7, 1700, 64, True, (3,)),         # 378 row groups, causal: up to two work-groups of them a compute unit, no items
+    (11, 1700, 64, True, (3,)),        # 154 items, causal: ranges of 20 items against heads of 14 Q blocks (two passes per range)
 ])
 def test_unbalanced_heads(sp, H, N, d, causal, dense_heads):
     import torch
