@@ -146,7 +146,9 @@ int sparge_predict_static(const void* Q, const void* K, const sparge_desc* desc,
  * attention needs}; it is overwritten, not accumulated.
  * Work distribution: the launch is two resident workgroups per compute unit that take (head, Q block)
  * items: the first by position, further ones from eight counters (one per XCD range of items) kept in `ws` and set
- * by an earlier kernel of the call; which workgroup computes an item depends on timing, the result does not.
+ * by an earlier kernel of the call; which workgroup computes an item depends on timing, the result does not.  A call of
+ * few 32-row groups (no more than compute units; causal, up to twice as many where rows are long) gives each group a
+ * workgroup of its own instead, with the same result bit for bit.
  */
 int sparge_attn_quantized(const int8_t* Qq, const int8_t* Kq, const float* q_scale, const float* k_scale,
                           const void* V, const sparge_desc* desc, const uint8_t* mask,
@@ -155,7 +157,9 @@ int sparge_attn_quantized(const int8_t* Qq, const int8_t* Kq, const float* q_sca
 
 /*
  * Diagnostic, host only (no GPU work): the order in which the attention kernel hands out its (batch, head,
- * Q block) items for this shape.  order: host array of B*H*T_m entries; entry n is (b*H + h)*T_m + i.  The items
+ * Q block) items for this shape.  (Calls of few row groups hand out no items: their 32-row groups are workgroups of one
+ * launch, eight contiguous ranges of them, by ascending group or, causal, each head's last group first; for such a
+ * shape the list is the order that a call too large for that would take.)  order: host array of B*H*T_m entries; entry n is (b*H + h)*T_m + i.  The items
  * are cut into eight contiguous ranges (one per XCD), listed here one after the other; a range hands its items
  * out in the listed order, the ranges run side by side, and a work-group whose range is empty takes from the
  * next.  Non-causal: index order.  Causal: per range, first the later (longer) half of every head's Q blocks,

@@ -377,7 +377,7 @@ def sparge_tune(inputs, tau_grid, theta_grid, lambda_grid, l1: float, l2: float,
 
 def sparge_item_order(B: int, H: int, N: int, d: int = 128, causal: bool = False) -> torch.Tensor:
     """-> int32 [B*H*Tm] (CPU tensor): the attention kernel's items (b*H + h)*Tm + i in hand-out order, the eight
-    ranges one after the other (diagnostic; runs on the host)."""
+    ranges one after the other (diagnostic; runs on the host; calls of few row groups hand out none)."""
     desc = _Desc(B, H, N, d, 1, H * N * d, N * d, d, 0, 0)
     n = B * H * _blocks(N)[0]
     buf = (ctypes.c_int32 * max(n, 1))()

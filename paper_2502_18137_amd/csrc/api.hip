@@ -172,7 +172,7 @@ int check_lambda(const float* lambda, int H, HeadParams* l) {
 // Block statistics of Q and K, Q quantization, K mean, K quantization (any output may be skipped).
 // A second stream per device (default priority) with the two events of a fork and join.  The forward
 // pass puts the passes nobody waits for early (K mean, K quantization, V tiles: bandwidth-bound) there,
-// beside the block predictor (fp64 matrix products and a sort: neither bandwidth-bound), and joins before
+// beside the block predictor (fp64 matrix products and a ranking: neither bandwidth-bound), and joins before
 // the attention kernel.  Created on first use, kept until the process ends; no second stream (creation
 // failed, or more devices than slots) means everything runs on the caller's stream.
 struct SideStream {

@@ -1,7 +1,8 @@
 """The attention kernel's work-item order, through the library's host-side diagnostic (no GPU needed): every
 (batch, head, Q block) exactly once whatever the shape, index order without a causal mask, and with one the
 property the order exists for -- inside each of the eight ranges the later (longer) half of every head's rows
-comes before any earlier half, longest first inside a head."""
+comes before any earlier half, longest first inside a head.  (Calls of few row groups run a workgroup per group and hand out no
+items; what they compute is compared with the items of larger calls on the GPU.)"""
 import numpy as np
 import pytest
 
