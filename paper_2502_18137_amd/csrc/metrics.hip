@@ -16,14 +16,17 @@ __global__ __launch_bounds__(1024) void rel_l1_kernel(const uint16_t* __restrict
     __shared__ double red[2][1024];
     const int h = blockIdx.x, b = blockIdx.y;
     const long long base = b * s.sb + h * s.sh;
-    const int op = s.operand(b * s.H + h);   // (Shape: settings of one launch, measured against one reference)
-    const long long ref_base = op / s.H * s.sb + op % s.H * s.sh;
+    if (b * s.H + h >= s.op_bh) {   // (Shape: settings of one launch, measured against one reference)
+        asm volatile("");           // an ordinary call does none of these divisions
+        const int op = s.operand(b * s.H + h);
+        Oref += op / s.H * s.sb + op % s.H * s.sh - base;
+    }
     const int col = threadIdx.x % CPR, r0 = threadIdx.x / CPR;
     double num = 0.0, den = 0.0;
     for (int row = r0; row < s.N; row += RPI) {
-        const long long off = (long long)row * s.sn + col * 8;
-        const uint4 a = *reinterpret_cast<const uint4*>(O + base + off);
-        const uint4 r = *reinterpret_cast<const uint4*>(Oref + ref_base + off);
+        const long long off = base + (long long)row * s.sn + col * 8;
+        const uint4 a = *reinterpret_cast<const uint4*>(O + off);
+        const uint4 r = *reinterpret_cast<const uint4*>(Oref + off);
         const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, rw[4] = {r.x, r.y, r.z, r.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
